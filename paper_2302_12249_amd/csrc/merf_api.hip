@@ -161,7 +161,9 @@ Layout make_layout(const merf_scene_desc *d, int64_t nbricks) {
     const size_t rf = (size_t)d->occ_res[d->occ_levels - 1];
     o.dist = off; off = align_up(off + (rf <= (size_t)kOctMaxRes ? 8 : 1) * rf * rf * rf, 256);
     o.mlp = off; off = align_up(off + kMlpParams * sizeof(float), 256);
-    o.total = off;
+    // a footprint at the planes' last texels reads a row and a texel pair past
+    // them (with weight 0): the allocation reaches that far
+    o.total = std::max(off, align_up(o.planes + 3 * R * R * kChannels + (R + 2) * kChannels, 256));
     return o;
 }
 
@@ -572,6 +574,13 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
     ds.planes_w = R > 0 ? 1.0f : 0.0f;
     ds.dist_scale = (float)ds.dist_res * 0.25f;
     ds.dist_off = 2.0f * ds.dist_scale;
+    ds.dist_max = (float)(ds.dist_res - 1);
+    ds.dist_resf = (float)ds.dist_res;
+    ds.dist_centre = 0.5f * ds.dist_cell - 2.0f;
+    ds.dist_slice = (uint32_t)ds.dist_res * (uint32_t)ds.dist_res;
+    constexpr double kNegLog2e = -1.4426950408889634;
+    ds.f_scale24_l2 = (float)(kNegLog2e * (double)ds.f_scale24);
+    ds.f_off_l2 = (float)(kNegLog2e * (double)ds.f_off);
     {
         std::lock_guard<std::mutex> lk(g_mutex);
         g_live.insert(s);

@@ -81,6 +81,9 @@ struct DevScene {
     float f_scale, f_off;                        // appearance: 2 m_f / 255 and -nsrc m_f
     float d_scale24, f_scale24;                  // d_scale, f_scale times 2^24 (codes read as b * 2^-24)
     float dist_scale, dist_off;                  // empty-space cell: fma(p, r_f/4, r_f/2)
+    float dist_max, dist_resf, dist_centre;      // r_f - 1, r_f, centre of cell 0: dist_cell / 2 - 2
+    uint32_t dist_slice;                         // r_f^2
+    float f_scale24_l2, f_off_l2;                // -log2(e) f_scale24 and f_off: the exponent of a sigmoid
 };
 
 struct DevCamera {

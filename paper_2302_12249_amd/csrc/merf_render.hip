@@ -44,6 +44,7 @@ namespace {
 
 constexpr float kInf = __builtin_huge_valf();
 constexpr float kRcp255 = 1.0f / 255.0f;
+constexpr float kNegLog2e = -1.44269504088896340736f;
 // Samples are never skipped past a cell exit by more than this (contracted
 // units): FP32 error of the exit parameter is below 1e-6.
 constexpr float kSkipGuard = 2e-6f;
@@ -219,7 +220,10 @@ __device__ __forceinline__ int lanes_below(uint64_t m) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-__device__ __forceinline__ float sigmoid(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
+// Sigmoid of x given as -x log2(e).
+__device__ __forceinline__ float sigmoid_l2(float x) {
+    return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x));
+}
 
 // XCD-aware tile order.  Consecutive workgroups are dispatched round-robin
 // over the 8 XCDs (workgroup b runs on XCD b % 8 as that XCD's (b / 8)-th),
@@ -282,7 +286,12 @@ __device__ __forceinline__ u32x4 load_pair(const uint8_t *base, uint32_t off) {
 // Byte offsets of the 20 texels one sample reads.  Planes: the (u, v) and
 // (u + 1, v) texels of row v start at op[p] and those of row v + 1 at
 // op[p] + prow.  Grid: the 2x2x2 footprint of brick slot brick_index[bi]
-// starts at byte ol of that brick.
+// starts at byte ol of that brick.  A coordinate clamped to the last texel has
+// that texel as its low one and fraction 0: the high one then lies past the
+// row, the plane or (planes) the array, is read with weight 0 and changes
+// nothing (any byte is a finite code; the scene's allocation reaches a row
+// past the planes).  That leaves a floor and a fraction per axis, two
+// instructions fewer than clamping the low texel to the last but one.
 struct Footprint {
     uint32_t op[3], prow, bi, ol;
     float ex, ey, ez;   // plane texel fractions
@@ -300,8 +309,8 @@ __device__ __forceinline__ Footprint footprint(const S &sc, float3 p) {
     float hx = __builtin_amdgcn_fmed3f(fmaf(p.x, ps, ps2), 0.0f, pmax);
     float hy = __builtin_amdgcn_fmed3f(fmaf(p.y, ps, ps2), 0.0f, pmax);
     float hz = __builtin_amdgcn_fmed3f(fmaf(p.z, ps, ps2), 0.0f, pmax);
-    int jx = min((int)hx, sc.R - 2), jy = min((int)hy, sc.R - 2), jz = min((int)hz, sc.R - 2);
-    f.ex = hx - (float)jx; f.ey = hy - (float)jy; f.ez = hz - (float)jz;
+    const int jx = (int)hx, jy = (int)hy, jz = (int)hz;
+    f.ex = __builtin_amdgcn_fractf(hx); f.ey = __builtin_amdgcn_fractf(hy); f.ez = __builtin_amdgcn_fractf(hz);
     const uint32_t row = (uint32_t)sc.R * kChannels, plane = (uint32_t)sc.R * row;
     f.prow = row;
     // (R <= 8192: texel indices and the row of 8 R bytes are below 2^24, and
@@ -314,8 +323,8 @@ __device__ __forceinline__ Footprint footprint(const S &sc, float3 p) {
     float gx = __builtin_amdgcn_fmed3f(fmaf(p.x, gs, gs2), 0.0f, gmax);
     float gy = __builtin_amdgcn_fmed3f(fmaf(p.y, gs, gs2), 0.0f, gmax);
     float gz = __builtin_amdgcn_fmed3f(fmaf(p.z, gs, gs2), 0.0f, gmax);
-    int ix = min((int)gx, sc.L - 2), iy = min((int)gy, sc.L - 2), iz = min((int)gz, sc.L - 2);
-    f.fx = gx - (float)ix; f.fy = gy - (float)iy; f.fz = gz - (float)iz;
+    const int ix = (int)gx, iy = (int)gy, iz = (int)gz;
+    f.fx = __builtin_amdgcn_fractf(gx); f.fy = __builtin_amdgcn_fractf(gy); f.fz = __builtin_amdgcn_fractf(gz);
     f.bi = mul24((uint32_t)(iz >> 3), mul24((uint32_t)sc.nbl, (uint32_t)sc.nbl)) +
            mul24((uint32_t)(iy >> 3), (uint32_t)sc.nbl) + (uint32_t)(ix >> 3);
     f.ol = (uint32_t)((((iz & 7) * kBrick + (iy & 7)) * kBrick + (ix & 7)) * kChannels);
@@ -437,7 +446,9 @@ __device__ __forceinline__ SampleResult eval_sample(const S &sc, float3 p, float
     SampleResult r;
     float tau = __expf(s0);                       // Eq. 6
     r.trans = __expf(-tau * delta);               // e^{-tau delta} = 1 - alpha (Eq. 1)
-    if (1.0f - r.trans > 0.0f) {
+    // (appearance of every lane: where alpha is zero its weight is zero, and
+    // a wave with no other lane practically never occurs)
+    {
         float sa[7];
 #pragma unroll
         for (int c = 0; c < 7; ++c) sa[c] = 0.0f;
@@ -457,7 +468,7 @@ __device__ __forceinline__ SampleResult eval_sample(const S &sc, float3 p, float
                 sa[6] = __builtin_amdgcn_fdot2(wk, codes_jj<3>(ha, hb), sa[6], false);
             }
 #pragma unroll
-            for (int c = 0; c < 7; ++c) sa[c] = fmaf(sa[c], sc.f_scale24, sc.f_off);
+            for (int c = 0; c < 7; ++c) sa[c] = fmaf(sa[c], sc.f_scale24_l2, sc.f_off_l2);
         } else if constexpr (kFeat == 1) {
             const float af = sc.f_scale24;
 #pragma unroll
@@ -472,6 +483,8 @@ __device__ __forceinline__ SampleResult eval_sample(const S &sc, float3 p, float
                 sa[5] = fmaf(w[i], deq_f16(h02.y, af, mf), sa[5]);
                 sa[6] = fmaf(w[i], deq_f16(h13.y, af, mf), sa[6]);
             }
+#pragma unroll
+            for (int c = 0; c < 7; ++c) sa[c] *= kNegLog2e;
         } else {
             // per texel pair: channel 2 of both texels from one permute, so
             // 7 permutes or masks extract the 14 codes of the pair
@@ -493,13 +506,10 @@ __device__ __forceinline__ SampleResult eval_sample(const S &sc, float3 p, float
                 }
             }
 #pragma unroll
-            for (int c = 0; c < 7; ++c) sa[c] = fmaf(sa[c], sc.f_scale24, sc.f_off);
+            for (int c = 0; c < 7; ++c) sa[c] = fmaf(sa[c], sc.f_scale24_l2, sc.f_off_l2);
         }
 #pragma unroll
-        for (int c = 0; c < 7; ++c) r.sg[c] = sigmoid(sa[c]);
-    } else {
-#pragma unroll
-        for (int c = 0; c < 7; ++c) r.sg[c] = 0.0f;
+        for (int c = 0; c < 7; ++c) r.sg[c] = sigmoid_l2(sa[c]);
     }
     return r;
 }
@@ -530,7 +540,8 @@ struct Segment {
     float3 A, e;                    // contracted start, unit direction
     float len, iex, iey, iez;       // length; inverse direction (+-inf where e = +-0)
     float tb;                       // world parameter of the end (kInf: last)
-    int n, k, reg, reg_next;        // interval count, next interval, regions
+    float n, k;                     // interval count, next interval (integers below 2^24)
+    int reg, reg_next;              // regions
     uint32_t doff;                  // byte offset of the empty-space grid of this direction's octant
 };
 
@@ -610,11 +621,11 @@ __device__ __forceinline__ void open_segment(float3 o, float3 d, float ta, int r
     s.reg_next = reg_next;
     float3 e = make_float3(B.x - s.A.x, B.y - s.A.y, B.z - s.A.z);
     float len = sqrtf(e.x * e.x + e.y * e.y + e.z * e.z);
-    s.k = 0;
+    s.k = 0.0f;
     // contracted segments are at most a few units long; anything else is a
     // degenerate ray (NaN / infinite end point) and contributes nothing
     if (!(len > 0.0f && len < 16.0f)) {
-        s.n = 0;
+        s.n = 0.0f;
         s.len = 0.0f;
         return;
     }
@@ -622,7 +633,7 @@ __device__ __forceinline__ void open_segment(float3 o, float3 d, float ta, int r
     e.x *= il; e.y *= il; e.z *= il;
     s.e = e;
     s.len = len;
-    s.n = (int)ceilf(len * istep);
+    s.n = ceilf(len * istep);       // (len < 16 and a step of at least 1e-6)
     // rcp(+-0) = +-inf: the slab tests below then give +inf (or NaN, which
     // fminf ignores) for an axis the segment does not move along
     s.iex = rcp(e.x);
@@ -631,40 +642,59 @@ __device__ __forceinline__ void open_segment(float3 o, float3 d, float ta, int r
     s.doff = oct_stride * (uint32_t)((s.iex < 0.0f ? 1 : 0) | (s.iey < 0.0f ? 2 : 0) | (s.iez < 0.0f ? 4 : 0));
 }
 
+// Lattice interval k of a segment: its ends u0, u1 (the last interval is
+// shortened) and midpoint um.
+__device__ __forceinline__ void interval(const Segment &s, float step, float &u0, float &u1, float &um) {
+    u0 = s.k * step;
+    u1 = __builtin_amdgcn_fmed3f(u0 + step, 0.0f, s.len);
+    um = 0.5f * (u0 + u1);
+}
+
 // Empty-space grid of the segment's octant at contracted point p.  Returns
 // the byte D of p's cell: D > 0 means the cube of D cells a side with a
 // corner at that cell, extending the way the segment travels, is empty; 0
 // means the cell is occupied (the cube is the cell itself).  ue is the
 // segment parameter at which the cube ends (slab test).
+// The march is bound by instruction issue, so the cell is clamped and floored
+// as a float, which the row offset and the slab test both use, and the far
+// face of the cube is the cell's centre plus |D - 1/2| cells with the sign of
+// the direction: 29 vector instructions from the point to ue, where selecting
+// the face per axis from integer cells took 42.  With a power-of-two
+// resolution the face is exact, so ue has the value that the integer form
+// gives.  (Multiplying centre and half edge by 1 / e separately saves three
+// more instructions, but an ulp of ue then decided one sample in some ten
+// million otherwise; the signs as float16 operands of mixed-precision FMAs
+// save the same three and were 1.5% slower over a frame.)  An axis without
+// motion (1 / e infinite) gives +inf or NaN, which fminf ignores.
+// With the sample's own arithmetic below (floor and fraction of a texel
+// coordinate, sigmoid exponents scaled at upload, no branch on alpha) the
+// 1080p frame fell from 5020 to 4540 vector instructions per wave, 309 to
+// 289 us; 128x128 from 54.5 to 47 us, sixteen 1080p views 3.75 to 3.51 ms.
 template <typename S>
-__device__ __forceinline__ int dist_lookup(const S &sc, const Segment &s, float3 p, float &ue) {
-    const int r = sc.dist_res;
-    // cell of p: (p + 2) r / 4 rounded down (contracted points have p >= -2
-    // up to rounding, so truncation is the floor), clamped to the grid
-    const float os = sc.dist_scale, os2 = sc.dist_off;
-    const int qx = cell_index(fmaf(p.x, os, os2), r);
-    const int qy = cell_index(fmaf(p.y, os, os2), r);
-    const int qz = cell_index(fmaf(p.z, os, os2), r);
-    const int D = load_at<uint8_t>(sc.dist, s.doff + cell_offset(qx, qy, qz, r));
-    const int ext = D > 0 ? D - 1 : 0;
-    const float h = sc.dist_cell;
-    const float bx = (float)(s.iex > 0.0f ? qx + ext + 1 : qx - ext) * h - 2.0f;
-    const float by = (float)(s.iey > 0.0f ? qy + ext + 1 : qy - ext) * h - 2.0f;
-    const float bz = (float)(s.iez > 0.0f ? qz + ext + 1 : qz - ext) * h - 2.0f;
-    const float tx = (bx - s.A.x) * s.iex;
-    const float ty = (by - s.A.y) * s.iey;
-    const float tz = (bz - s.A.z) * s.iez;
+__device__ __forceinline__ uint32_t dist_lookup(const S &sc, const Segment &s, float3 p, float &ue) {
+    // cell of p: (p + 2) r / 4 clamped to [0, r - 1], rounded down
+    const float os = sc.dist_scale, os2 = sc.dist_off, qmax = sc.dist_max;
+    const float qx = floorf(__builtin_amdgcn_fmed3f(fmaf(p.x, os, os2), 0.0f, qmax));
+    const float qy = floorf(__builtin_amdgcn_fmed3f(fmaf(p.y, os, os2), 0.0f, qmax));
+    const float qz = floorf(__builtin_amdgcn_fmed3f(fmaf(p.z, os, os2), 0.0f, qmax));
+    // (r <= 1024: y r + x is exact in float32, z r^2 in a 24-bit multiply)
+    const uint32_t off = mul24((uint32_t)qz, (uint32_t)sc.dist_slice) + (uint32_t)fmaf(qy, sc.dist_resf, qx) + s.doff;
+    const uint32_t D = load_at<uint8_t>(sc.dist, off);
+    const float h = sc.dist_cell, c = sc.dist_centre;
+    const float half = fabsf(fmaf((float)D, h, -0.5f * h));
+    const float tx = (fmaf(qx, h, c) + copysignf(half, s.iex) - s.A.x) * s.iex;
+    const float ty = (fmaf(qy, h, c) + copysignf(half, s.iey) - s.A.y) * s.iey;
+    const float tz = (fmaf(qz, h, c) + copysignf(half, s.iez) - s.A.z) * s.iez;
     ue = fminf(tx, fminf(ty, tz));
     return D;
 }
 
 // Next lattice interval after leaving empty space at segment parameter
-// uexit: the first whose midpoint lies past the exit, and at least k + 1.
-__device__ __forceinline__ int skip_past(const Segment &s, float uexit, float istep) {
-    const float kn = floorf((uexit - kSkipGuard) * istep - 0.5f) + 1.0f;
-    // clamped to [0, n] (the float-to-int conversion saturates; NaN gives 0)
-    const int knext = min((int)fmaxf(kn, 0.0f), s.n);
-    return max(s.k + 1, knext);
+// uexit: the first whose midpoint lies past the exit less kSkipGuard, at
+// least k + 1 and at most n (k < n; a median, so NaN would give k + 1).
+__device__ __forceinline__ float skip_past(const Segment &s, float uexit, float istep) {
+    const float kn = floorf(fmaf(uexit, istep, 0.5f - kSkipGuard * istep));
+    return __builtin_amdgcn_fmed3f(kn, s.k + 1.0f, s.n);
 }
 
 // Pinhole ray through the centre of pixel (px, py) (unit direction).
@@ -937,7 +967,11 @@ __device__ __forceinline__ void render_tile(const S &sc, const Cam &cam, int lt,
         open_segment(o, d, 0.0f, region_at(o, d, c1 < kInf ? 0.5f * c1 : 1.0f), istep, sc.dist_oct_stride, s);
     }
     int nseg = 1;
-    bool alive = active, terminated = false;
+    // samples this lane may park: kQueue while its ray is marching, 0 once the
+    // ray has ended (a comparison with pc gives the wave mask of either state
+    // in one instruction, where a flag costs two)
+    int room = active ? kQueue : 0;
+    bool terminated = false;
     float known[kMaxLevels] = {0.0f, 0.0f, 0.0f, 0.0f};   // per level: occupied up to this u
     if (kPhase) ph.lap(kPhSetup);
 
@@ -957,7 +991,7 @@ __device__ __forceinline__ void render_tile(const S &sc, const Cam &cam, int lt,
     rs[2 * lane + 1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     int *imap = reinterpret_cast<int *>(rs + 2 * 64);          // [64] shading slot -> parked entry
     int pc = 0;                                               // samples parked by this lane
-    while (__any(alive || pc > 0)) {
+    while (__builtin_amdgcn_ballot_w64((room | pc) > 0) != 0) {
         if (kPhase) ph.count(kPhRounds);
         // ---- march: live lanes park up to kQueue samples, one step per
         // pass; the wave stops once 64 samples are parked (a round shades no
@@ -966,21 +1000,21 @@ __device__ __forceinline__ void render_tile(const S &sc, const Cam &cam, int lt,
         // compositing, then those marching or in the deferred MLP (the same
         // images; the frames are about 1% faster at 1080p and 2% at 4K)
         __builtin_amdgcn_s_setprio(0);
-        for (;;) {
-            const bool want = alive && pc < kQueue;
-            int parked = 0;
+        int parked = 0;                                       // by the whole wave
 #pragma unroll
-            for (int j = 0; j < kQueue; ++j) parked += __popcll(__ballot(pc > j));
-            if (!__any(want) || parked >= 64) break;
+        for (int j = 0; j < kQueue; ++j) parked += __popcll(__builtin_amdgcn_ballot_w64(pc > j));
+        for (;;) {
+            const bool want = pc < room;
+            if (__builtin_amdgcn_ballot_w64(want) == 0 || parked >= 64) break;
             if (kPhase) ph.count(kPhMarchPasses);
-            // a lane whose segment is done spends this pass on the next
-            // region's segment, if any
+            // a lane whose segment is done opens the next region's segment,
+            // if any, and marches on in the same pass
             const bool open = want && s.k >= s.n;
-            if (kPhase ? __any(open) : true) {
+            if (kPhase ? __builtin_amdgcn_ballot_w64(open) != 0 : true) {
                 if (kPhase) ph.lap(kPhMarch);
                 if (open) {
                     if (!(s.tb < kInf) || nseg >= 8) {
-                        alive = false;
+                        room = 0;
                     } else {
                         open_segment(o, d, s.tb, s.reg_next, istep, sc.dist_oct_stride, s);
                         ++nseg;
@@ -993,105 +1027,105 @@ __device__ __forceinline__ void render_tile(const S &sc, const Cam &cam, int lt,
                     ph.count(kPhOpenPasses);
                 }
             }
-            if (!want || open) continue;
-            // ---- one march step
-            const float u0 = (float)s.k * step;
-            const float u1 = fminf(u0 + step, s.len);
-            const float um = 0.5f * (u0 + u1);
-            const float3 p = make_float3(fmaf(um, s.e.x, s.A.x), fmaf(um, s.e.y, s.A.y), fmaf(um, s.e.z, s.A.z));
-            if (kStats) ++cnt.visited;
-            // empty >= 0: the sample is in empty space, which the segment
-            // leaves at parameter uexit.  A cell seen occupied stays known
-            // until the segment leaves it (its exit minus the guard), so later
-            // samples inside it need no lookup.
-            int empty = -1;
-            float uexit = 0.0f;
-            if constexpr (!kLevels) {
-                // empty-space grid: leave the whole empty cube ahead, or
-                // remember the occupied cell
-                if (!(um < known[0])) {
-                    if (kStats) ++cnt.occ_lookups;
-                    float ue;
-                    const int D = dist_lookup(sc, s, p, ue);
-                    if (D == 0) {
-                        known[0] = ue - kSkipGuard;
-                    } else {
-                        empty = 0;
-                        uexit = ue;
-                    }
-                }
-            } else {
-                // the occupancy levels, coarse to fine: stop at the first
-                // empty level and leave its cell
-#pragma unroll
-                for (int l = 0; l < kMaxLevels; ++l) {
-                    if (l < sc.occ_levels && empty < 0 && !(um < known[l])) {
-                        const int rl = sc.occ_res[l];
-                        const float os = (float)rl * 0.25f, os2 = 2.0f * os;
-                        const int qx = cell_index(fmaf(p.x, os, os2), rl);
-                        const int qy = cell_index(fmaf(p.y, os, os2), rl);
-                        const int qz = cell_index(fmaf(p.z, os, os2), rl);
+            const int pc0 = pc;
+            if (want && s.k < s.n) {
+                // ---- one march step
+                float u0, u1, um;
+                interval(s, step, u0, u1, um);
+                const float3 p = make_float3(fmaf(um, s.e.x, s.A.x), fmaf(um, s.e.y, s.A.y), fmaf(um, s.e.z, s.A.z));
+                if (kStats) ++cnt.visited;
+                // a sample in empty space moves the march past the point where
+                // the segment leaves it.  A cell seen occupied stays known
+                // until the segment leaves it (its exit minus the guard), so
+                // later samples inside it need no lookup.
+                bool occupied = true;
+                if constexpr (!kLevels) {
+                    // empty-space grid: leave the whole empty cube ahead, or
+                    // remember the occupied cell
+                    if (!(um < known[0])) {
                         if (kStats) ++cnt.occ_lookups;
-                        const bool occ = load_at<uint8_t>(sc.occ[l], cell_offset(qx, qy, qz, rl)) != 0;
-                        // exit parameter of this cell along the segment (slab test)
-                        const float h = sc.occ_cell[l];
-                        const float bx = (float)(s.iex > 0.0f ? qx + 1 : qx) * h - 2.0f;
-                        const float by = (float)(s.iey > 0.0f ? qy + 1 : qy) * h - 2.0f;
-                        const float bz = (float)(s.iez > 0.0f ? qz + 1 : qz) * h - 2.0f;
-                        const float tx = (bx - s.A.x) * s.iex;
-                        const float ty = (by - s.A.y) * s.iey;
-                        const float tz = (bz - s.A.z) * s.iez;
-                        const float ue = fminf(tx, fminf(ty, tz));
-                        if (occ) {
-                            known[l] = ue - kSkipGuard;
+                        float ue;
+                        if (dist_lookup(sc, s, p, ue) == 0) {
+                            known[0] = ue - kSkipGuard;
                         } else {
-                            empty = l;
-                            uexit = ue;
+                            occupied = false;
+                            s.k = skip_past(s, ue, istep);
                         }
                     }
+                } else {
+                    // the occupancy levels, coarse to fine: stop at the first
+                    // empty level and leave its cell
+                    float uexit = 0.0f;
+#pragma unroll
+                    for (int l = 0; l < kMaxLevels; ++l) {
+                        if (l < sc.occ_levels && occupied && !(um < known[l])) {
+                            const int rl = sc.occ_res[l];
+                            const float os = (float)rl * 0.25f, os2 = 2.0f * os;
+                            const int qx = cell_index(fmaf(p.x, os, os2), rl);
+                            const int qy = cell_index(fmaf(p.y, os, os2), rl);
+                            const int qz = cell_index(fmaf(p.z, os, os2), rl);
+                            if (kStats) ++cnt.occ_lookups;
+                            const bool occ = load_at<uint8_t>(sc.occ[l], cell_offset(qx, qy, qz, rl)) != 0;
+                            // exit parameter of this cell along the segment (slab test)
+                            const float h = sc.occ_cell[l];
+                            const float bx = (float)(s.iex > 0.0f ? qx + 1 : qx) * h - 2.0f;
+                            const float by = (float)(s.iey > 0.0f ? qy + 1 : qy) * h - 2.0f;
+                            const float bz = (float)(s.iez > 0.0f ? qz + 1 : qz) * h - 2.0f;
+                            const float tx = (bx - s.A.x) * s.iex;
+                            const float ty = (by - s.A.y) * s.iey;
+                            const float tz = (bz - s.A.z) * s.iez;
+                            const float ue = fminf(tx, fminf(ty, tz));
+                            if (occ) {
+                                known[l] = ue - kSkipGuard;
+                            } else {
+                                occupied = false;
+                                uexit = ue;
+                            }
+                        }
+                    }
+                    if (!occupied) s.k = skip_past(s, uexit, istep);
+                }
+                if (occupied) {
+                    float delta = u1 - u0;
+                    if (tp.delta_mode == 1) {
+                        float3 y0 = make_float3(fmaf(u0, s.e.x, s.A.x), fmaf(u0, s.e.y, s.A.y), fmaf(u0, s.e.z, s.A.z));
+                        float3 y1 = (s.k == s.n - 1.0f)
+                                        ? segment_end(o, d, s.tb, s.reg)
+                                        : make_float3(fmaf(u1, s.e.x, s.A.x), fmaf(u1, s.e.y, s.A.y), fmaf(u1, s.e.z, s.A.z));
+                        bool at_inf = false;
+                        if (s.reg != 0) {
+                            const int jj = (s.reg - 1) >> 1;
+                            const float sg = ((s.reg - 1) & 1) ? -1.0f : 1.0f;
+                            const float y1j = jj == 0 ? y1.x : (jj == 1 ? y1.y : y1.z);
+                            at_inf = sg * y1j >= 2.0f;
+                        }
+                        if (at_inf) {
+                            delta = kInf;
+                        } else {
+                            float3 x0 = unmap_region(s.reg, y0), x1 = unmap_region(s.reg, y1);
+                            float dx = x1.x - x0.x, dy = x1.y - x0.y, dz = x1.z - x0.z;
+                            delta = sqrtf(dx * dx + dy * dy + dz * dz);
+                        }
+                    }
+                    pq[pc * 64 + lane] = make_float4(p.x, p.y, p.z, delta);
+                    ++pc;
+                    s.k += 1.0f;
                 }
             }
-            if (empty < 0) {
-                float delta = u1 - u0;
-                if (tp.delta_mode == 1) {
-                    float3 y0 = make_float3(fmaf(u0, s.e.x, s.A.x), fmaf(u0, s.e.y, s.A.y), fmaf(u0, s.e.z, s.A.z));
-                    float3 y1 = (s.k == s.n - 1)
-                                    ? segment_end(o, d, s.tb, s.reg)
-                                    : make_float3(fmaf(u1, s.e.x, s.A.x), fmaf(u1, s.e.y, s.A.y), fmaf(u1, s.e.z, s.A.z));
-                    bool at_inf = false;
-                    if (s.reg != 0) {
-                        const int jj = (s.reg - 1) >> 1;
-                        const float sg = ((s.reg - 1) & 1) ? -1.0f : 1.0f;
-                        const float y1j = jj == 0 ? y1.x : (jj == 1 ? y1.y : y1.z);
-                        at_inf = sg * y1j >= 2.0f;
-                    }
-                    if (at_inf) {
-                        delta = kInf;
-                    } else {
-                        float3 x0 = unmap_region(s.reg, y0), x1 = unmap_region(s.reg, y1);
-                        float dx = x1.x - x0.x, dy = x1.y - x0.y, dz = x1.z - x0.z;
-                        delta = sqrtf(dx * dx + dy * dy + dz * dz);
-                    }
-                }
-                pq[pc * 64 + lane] = make_float4(p.x, p.y, p.z, delta);
-                ++pc;
-                ++s.k;
-            } else {
-                // leave the empty cell: first lattice interval whose midpoint
-                // lies past the exit
-                s.k = skip_past(s, uexit, istep);
-            }
+            parked += __popcll(__builtin_amdgcn_ballot_w64(pc != pc0));
         }
         if (kPhase) ph.lap(kPhMarch);
         // ---- shade: parked samples numbered level by level (all first
         // samples, then all second ones ...), lane order within a level;
         // slots past 64 wait for the next round
         int total = 0;
+        uint64_t level[kQueue];                               // lanes with more than j parked samples
 #pragma unroll
         for (int j = 0; j < kQueue; ++j) {
-            const int item = total + lanes_below(__ballot(pc > j));
+            level[j] = __builtin_amdgcn_ballot_w64(pc > j);
+            const int item = total + lanes_below(level[j]);
             if (pc > j && item < 64) imap[item] = j * 64 + lane;
-            total += __popcll(__ballot(pc > j));
+            total += __popcll(level[j]);
         }
         __syncthreads();
         __builtin_amdgcn_s_setprio(2);
@@ -1113,8 +1147,8 @@ __device__ __forceinline__ void render_tile(const S &sc, const Cam &cam, int lt,
         int done = 0, before = 0;
 #pragma unroll
         for (int j = 0; j < kQueue; ++j) {
-            const int item = before + lanes_below(__ballot(pc > j));
-            before += __popcll(__ballot(pc > j));
+            const int item = before + lanes_below(level[j]);
+            before += __popcll(level[j]);
             if constexpr (!kStats) {
                 // branch-free: an unused slot reads the result area at item 0
                 // (always finite) and contributes with weight 0, which leaves
@@ -1135,7 +1169,7 @@ __device__ __forceinline__ void render_tile(const S &sc, const Cam &cam, int lt,
                 acc.T *= use ? ra.x : 1.0f;
                 done += use ? 1 : 0;
                 if (use && acc.T < tp.t_min) {   // early termination (Sec. 6)
-                    alive = false;
+                    room = 0;
                     terminated = true;
                 }
             } else if (j < pc && item < 64 && !terminated) {
@@ -1156,7 +1190,7 @@ __device__ __forceinline__ void render_tile(const S &sc, const Cam &cam, int lt,
                 composite<kStats>(acc, r, cnt);
                 ++done;
                 if (acc.T < tp.t_min) {          // early termination (Sec. 6)
-                    alive = false;
+                    room = 0;
                     terminated = true;
                 }
             }
@@ -1346,9 +1380,8 @@ __global__ __launch_bounds__(64) void k_tile_cost(const DevScene sc, const Rende
                 ++nseg;
                 continue;
             }
-            const float u0 = (float)s.k * step;
-            const float u1 = fminf(u0 + step, s.len);
-            const float um = 0.5f * (u0 + u1);
+            float u0, u1, um;
+            interval(s, step, u0, u1, um);
             const float3 p = make_float3(fmaf(um, s.e.x, s.A.x), fmaf(um, s.e.y, s.A.y), fmaf(um, s.e.z, s.A.z));
             float ue;
             if (dist_lookup(sc, s, p, ue) == 0) {
@@ -1359,7 +1392,7 @@ __global__ __launch_bounds__(64) void k_tile_cost(const DevScene sc, const Rende
                 }
                 T *= eval_sample<0>(sc, p, u1 - u0).trans;
                 if (++ev >= kCostEval || T < rb.t_min) break;
-                ++s.k;
+                s.k += 1.0f;
             } else {
                 s.k = skip_past(s, ue, istep);
             }

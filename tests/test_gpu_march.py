@@ -1,0 +1,80 @@
+"""GPU parity where the march and the gathers meet the ends of their ranges:
+samples at the last texels of every array (rays to infinity over all seven
+regions, whose last sample has weight one in world-interval mode), plane and
+grid resolutions that are small, odd or not powers of two, scenes whose planes
+end the device allocation, and occupancy resolutions whose cells are not exact
+in float32.  Bar as in gpu_helpers (2/255 on non-fragile pixels)."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gpu_helpers import check, gpu_render, say
+from scene_builders import dense_scene
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available(), "GPU tests need a GPU"
+    return t
+
+
+@pytest.fixture(scope="module")
+def merf():
+    from paper_2302_12249_amd import merf as m
+    m.load()
+    return m
+
+
+def _all_round(w, h):
+    """Views along the six axes from inside the cube, 100 degrees wide."""
+    poses = [synth.scenes._look_at(np.array([0.1, -0.2, 0.15]), np.array(f, float))
+             for f in ((1, .1, .2), (-1, .2, .1), (.1, 1, .2), (.2, -1, .1), (.1, .2, 1), (.2, .1, -1))]
+    return synth.make_cameras(poses, [(w, h)] * len(poses), hfov_deg=100.0)
+
+
+def _thin(L, R, occ=None, seed=5):
+    """Stored everywhere, faint: no ray terminates before the limit point."""
+    sc = dense_scene(L=L, R=R, occ_fine=occ, seed=seed)
+    rng = np.random.default_rng(seed)
+    sc.blocks[..., 0] = rng.integers(90, 118, sc.blocks.shape[:-1])
+    sc.planes[..., 0] = rng.integers(90, 118, sc.planes.shape[:-1])
+    return sc
+
+
+@pytest.mark.parametrize("L,R", [(16, 16), (16, 33), (24, 50), (64, 127), (16, 2), (16, 256), (0, 19), (40, 0)])
+@pytest.mark.parametrize("kw", [{}, {"delta_mode": 1}, {"delta_mode": 1, "feat_prec": "f16", "mlp_prec": "f16"},
+                                {"delta_mode": 1, "feat_prec": "f16_interp"}])
+def test_last_texels_match_oracle(torch, merf, L, R, kw):
+    cams = _all_round(29, 21)
+    sc = _thin(max(L, 16), max(R, 2))
+    if L == 0:
+        sc = synth.planes_only(sc)
+    if R == 0:
+        sc = dataclasses.replace(sc, R=0, planes=np.zeros((3, 0, 0, 8), np.uint8))
+    step = 4.0 / max(L, R)
+    say(f"last texels: L {L} R {R} {kw}")
+    gpu = gpu_render(torch, merf, sc, cams, step=step, **kw)
+    ref, st = oracle.render(sc, cams, step=step, delta_mode=kw.get("delta_mode", 0))
+    if "delta_mode" in kw:
+        assert ref[:, 3].min() >= 1.0 - 2e-4   # the last sample of every ray not ended before counts fully
+    check(gpu, ref, st["fragile"], f"L {L} R {R} {kw}", max_fragile=0.05)
+
+
+@pytest.mark.parametrize("rf,pools", [(4, (2, 1)), (6, (3, 1)), (10, (5, 1)), (16, (1,)), (18, (9, 3, 1)), (32, (8, 2, 1))])
+def test_empty_space_matches_levels_and_oracle(torch, merf, rf, pools):
+    rng = np.random.default_rng(rf)
+    occ = (rng.random((rf, rf, rf)) < 0.15).astype(np.uint8)
+    base = dense_scene(L=16, R=64, seed=rf)
+    sc = dataclasses.replace(base, occ=[(rf // p, synth.maxpool(occ, p) if p > 1 else occ) for p in pools])
+    cams = _all_round(61, 47)
+    say(f"empty space: {rf}^3 cells, pools {pools}")
+    gpu = gpu_render(torch, merf, sc, cams)
+    ref, st = oracle.render(sc, cams)
+    check(gpu, ref, st["fragile"], f"rf {rf}", max_fragile=0.05)
+    assert np.array_equal(gpu, gpu_render(torch, merf, sc, cams, skip="levels"))
