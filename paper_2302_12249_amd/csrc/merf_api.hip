@@ -870,11 +870,8 @@ int merf_occupancy_pyramid(const uint8_t *mask_dev, int32_t res, const int32_t *
             return fail(MERF_E_INVALID, "factor %d does not divide res %d", factors[l], res);
         if (!out_dev[l]) return fail(MERF_E_INVALID, "out_dev[%d] is NULL", l);
     }
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    for (int l = 0; l < n_levels; ++l) {
-        hipError_t e = launch_maxpool(mask_dev, res, factors[l], out_dev[l], stream);
-        if (e != hipSuccess) return hip_fail(e, "max-pool launch");
-    }
+    const hipError_t e = launch_maxpool(mask_dev, res, factors, n_levels, out_dev, static_cast<hipStream_t>(hip_stream));
+    if (e != hipSuccess) return hip_fail(e, "max-pool launch");
     return MERF_OK;
 }
 

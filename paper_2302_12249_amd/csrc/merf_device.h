@@ -195,7 +195,22 @@ hipError_t launch_dequant(const uint8_t *codes, int64_t n, float m, float a, int
 // merf_ingest.hip: brick_pos[i] = bx | by << 10 | bz << 20 of brick slot i.
 hipError_t launch_pack_bricks(const uint8_t *blocks, const int32_t *block_index, const int32_t *brick_pos,
                               int nbricks, int L, uint8_t *bricks, hipStream_t stream);
-hipError_t launch_maxpool(const uint8_t *in, int rin, int f, uint8_t *out, hipStream_t stream);
+// Max-pools a cubic mask of res cells a side by each of n factors (divisors
+// of res) into out[l] (0 / 1 bytes).
+constexpr int kMaxPoolLevels = 8;
+struct PoolLevel {
+    const uint8_t *in;                           // uint8 [rin^3]
+    uint8_t *out;                                // uint8 [(rin / factor)^3]
+    int32_t rin, factor;
+    int32_t rows, parts;                         // output rows a workgroup takes; workgroups that share them
+    int32_t first_block;                         // first workgroup of the level
+};
+struct PoolLevels {
+    PoolLevel level[kMaxPoolLevels];
+    int32_t n;
+};
+hipError_t launch_maxpool(const uint8_t *mask, int res, const int32_t *factors, int n, uint8_t *const *out,
+                          hipStream_t stream);
 // Distance grid of DevScene::dist from the occupancy levels (tmp0, tmp1:
 // scratch of r_f^3 bytes each).
 struct OccLevels {
