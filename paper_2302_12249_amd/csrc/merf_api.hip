@@ -468,9 +468,9 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
                  s_dist0 = s_pos + align_up(std::max<size_t>(bpos.size(), 1) * sizeof(int32_t), 256);
     const size_t rf = (size_t)desc->occ_res[desc->occ_levels - 1], nf = rf * rf * rf;
     const bool octants = rf <= (size_t)kOctMaxRes;
-    // distance scratch: seed + second byte grid, or seed + int32 prefix sums
+    // scratch of the empty-space grid: the octants', or two byte grids
     const size_t s_dist1 = s_dist0 + align_up(nf, 256),
-                 staging = s_dist1 + align_up(octants ? nf * sizeof(int32_t) : nf, 256);
+                 staging = octants ? s_dist0 + octant_scratch_bytes((int)rf) : s_dist1 + align_up(nf, 256);
     void *base = nullptr, *stage = nullptr;
     hipError_t e = dev_alloc(&base, total, ordered, stream);
     if (e == hipSuccess) e = dev_alloc(&stage, staging, ordered, stream);
@@ -516,8 +516,7 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
             lv.occ[l] = dev(o_occ[l]);
             lv.res[l] = desc->occ_res[l];
         }
-        e = octants ? launch_octant_extents(lv, stg(s_dist0), reinterpret_cast<int32_t *>(stg(s_dist1)),
-                                            dev(lay.dist), stream)
+        e = octants ? launch_octant_extents(lv, stg(s_dist0), dev(lay.dist), stream)
                     : launch_distance_grid(lv, stg(s_dist0), stg(s_dist1), dev(lay.dist), stream);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
@@ -926,8 +925,7 @@ int merf_octant_extent_grid(const uint8_t *const *occ_dev, const int32_t *res, i
     OccLevels lv;
     int rc = occ_levels_arg(occ_dev, res, n_levels, out_dev, lv);
     if (rc) return rc;
-    const size_t r = (size_t)res[n_levels - 1], n = r * r * r;
-    const size_t bytes = align_up(n, 256) + align_up(n * sizeof(int32_t), 256);
+    const size_t bytes = octant_scratch_bytes(res[n_levels - 1]);
     void *tmp = nullptr;
     hipError_t e = hipMalloc(&tmp, bytes);
     if (e != hipSuccess || !tmp) {
@@ -935,9 +933,7 @@ int merf_octant_extent_grid(const uint8_t *const *occ_dev, const int32_t *res, i
         return fail(MERF_E_OOM, "hipMalloc of %zu scratch bytes failed", bytes);
     }
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    uint8_t *seed = static_cast<uint8_t *>(tmp);
-    int32_t *sat = reinterpret_cast<int32_t *>(seed + align_up(n, 256));
-    e = launch_octant_extents(lv, seed, sat, out_dev, stream);
+    e = launch_octant_extents(lv, static_cast<uint8_t *>(tmp), out_dev, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     (void)hipFree(tmp);
     if (e != hipSuccess) return hip_fail(e, "octant extent grid");
