@@ -34,6 +34,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "merf_device.h"
@@ -1563,19 +1564,42 @@ __global__ __launch_bounds__(64) void k_gather_replay(const DevScene sc, const u
 // bfloat16, which is the correctly rounded bfloat16 value, because k/255
 // never lies within half a float32 ulp of a bfloat16 rounding boundary (its
 // binary expansion repeats with period 8); the test-suite checks all codes.
-__global__ void k_dequant(const uint8_t *__restrict__ codes, int64_t n, float m, float a, int prec,
-                          void *__restrict__ out) {
-    const float m2 = 2.0f * m, m255 = 255.0f * m;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        if (prec == 1) {
-            const _Float16 code = as_f16x2((uint32_t)codes[i]).x;     // the subnormal b 2^-24
-            reinterpret_cast<__half *>(out)[i] = __float2half_rn(deq_f16(code, a * 16777216.0f, m));
-        } else {
-            const float v = deq_f32(codes[i], m2, m255);
-            if (prec == 0) reinterpret_cast<float *>(out)[i] = v;
-            else reinterpret_cast<__hip_bfloat16 *>(out)[i] = __float2bfloat16(v);
+// Bound by its traffic (one byte read, two or four written a code): a thread
+// takes 16 codes as one vector and stores 16-byte vectors.  Buffers that are
+// not aligned to that take the codes one by one (kVec false), as do the last
+// n % 16.  Float16, 100.7 M codes: 55 us (5.5 TB/s, as a large copy), 142 us
+// with a code per thread.
+template <int prec>
+__device__ __forceinline__ auto dequant_one(uint32_t code, float m2, float m255, float m, float a24) {
+    if constexpr (prec == 1) return __float2half_rn(deq_f16(as_f16x2(code).x, a24, m));   // the subnormal b 2^-24
+    else if constexpr (prec == 0) return deq_f32(code, m2, m255);
+    else return __float2bfloat16(deq_f32(code, m2, m255));
+}
+
+template <int prec, bool kVec>
+__global__ __launch_bounds__(256) void k_dequant(const uint8_t *__restrict__ codes, int64_t n, float m, float a,
+                                                 void *__restrict__ out) {
+    using T = decltype(dequant_one<prec>(0u, 0.0f, 0.0f, 0.0f, 0.0f));
+    const float m2 = 2.0f * m, m255 = 255.0f * m, a24 = a * 16777216.0f;
+    T *o = reinterpret_cast<T *>(out);
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, nt = (int64_t)gridDim.x * blockDim.x;
+    int64_t first = 0;
+    if constexpr (kVec) {
+        for (int64_t i = t; i < n / 16; i += nt) {
+            const u32x4 v = reinterpret_cast<const u32x4 *>(codes)[i];
+            T x[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) x[k] = dequant_one<prec>(byte_of(v[k >> 2], k & 3), m2, m255, m, a24);
+#pragma unroll
+            for (int k = 0; k < (int)sizeof(T); ++k) {
+                u32x4 w;
+                __builtin_memcpy(&w, x + k * (16 / (int)sizeof(T)), 16);
+                reinterpret_cast<u32x4 *>(o + 16 * i)[k] = w;
+            }
         }
+        first = n / 16 * 16;
     }
+    for (int64_t i = first + t; i < n; i += nt) o[i] = dequant_one<prec>(codes[i], m2, m255, m, a24);
 }
 
 }  // namespace
@@ -1671,9 +1695,14 @@ hipError_t launch_gather_replay(const DevScene &sc, const uint32_t *rec, const i
 hipError_t launch_dequant(const uint8_t *codes, int64_t n, float m, float a, int prec, void *out,
                           hipStream_t stream) {
     if (n <= 0) return hipSuccess;
-    int64_t blocks = (n + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_dequant, dim3((unsigned)blocks), dim3(256), 0, stream, codes, n, m, a, prec, out);
+    const bool vec = reinterpret_cast<uintptr_t>(codes) % 16 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0;
+    // a vector per thread up to 2^17 workgroups, which 2^29 codes fill
+    const int64_t items = vec ? std::max<int64_t>(n / 16, std::min<int64_t>(n, 256)) : n;
+    const dim3 grid((unsigned)std::min<int64_t>((items + 255) / 256, vec ? 1 << 17 : 4096)), block(256);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, codes, n, m, a, out); };
+    if (prec == 0) vec ? launch(k_dequant<0, true>) : launch(k_dequant<0, false>);
+    else if (prec == 1) vec ? launch(k_dequant<1, true>) : launch(k_dequant<1, false>);
+    else vec ? launch(k_dequant<2, true>) : launch(k_dequant<2, false>);
     return hipGetLastError();
 }
 

@@ -86,3 +86,24 @@ def test_octant_extent_sizes(torch, merf, r, density):
     got = got[:, torch.from_numpy(cells[:, 2]).cuda(), torch.from_numpy(cells[:, 1]).cuda(),
               torch.from_numpy(cells[:, 0]).cuda()].cpu().numpy()
     assert np.array_equal(got, _extent_at(comb, cells))
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("n,off_in,off_out", [(1, 0, 0), (15, 0, 0), (16, 0, 0), (17, 0, 0), (4099, 0, 0), (65536, 0, 0),
+                                              (100, 1, 0), (300, 16, 3), (257, 5, 1), (70001, 0, 8)])
+def test_dequantize_sizes_and_alignments(torch, merf, prec, n, off_in, off_out):
+    """Every size and alignment gives the values of the 256 codes one by one,
+    and nothing past the n outputs is written."""
+    dt = [torch.float32, torch.float16, torch.bfloat16][prec]
+    rng = np.random.default_rng(n)
+    codes = torch.from_numpy(rng.integers(0, 256, n + off_in, dtype=np.uint8)).cuda()
+    out = torch.full((n + off_out + 8,), 99.0, dtype=dt, device="cuda")
+    table = torch.empty(256, dtype=dt, device="cuda")
+    one = torch.arange(256, dtype=torch.uint8, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    for c in range(256):                         # one code a call: the scalar form
+        merf.merf_dequantize(one.data_ptr() + c, 1, 7.0, prec, table.data_ptr() + c * table.element_size(), st)
+    merf.merf_dequantize(codes.data_ptr() + off_in, n, 7.0, prec, out.data_ptr() + off_out * out.element_size(), st)
+    torch.cuda.synchronize()
+    assert torch.equal(out[off_out:off_out + n], table[codes[off_in:].long()])
+    assert bool((out[:off_out] == 99.0).all()) and bool((out[off_out + n:] == 99.0).all())
