@@ -78,3 +78,17 @@ def test_empty_space_matches_levels_and_oracle(torch, merf, rf, pools):
     ref, st = oracle.render(sc, cams)
     check(gpu, ref, st["fragile"], f"rf {rf}", max_fragile=0.05)
     assert np.array_equal(gpu, gpu_render(torch, merf, sc, cams, skip="levels"))
+
+
+@pytest.mark.parametrize("size", [(1, 1), (2, 4), (3, 3), (4, 3), (13, 1), (4, 4), (17, 1), (3, 7), (8, 8)])
+@pytest.mark.parametrize("thin", [True, False])
+def test_few_rays_in_a_tile_match_oracle(torch, merf, size, thin):
+    """Tiles with few rays park more samples a round: long transparent rays
+    (every one runs to the limit point) and ordinary ones."""
+    sc = _thin(64, 127) if thin else dense_scene(L=32, R=64, seed=2)
+    cams = _all_round(*size)
+    say(f"few rays: {size} thin {thin}")
+    gpu = gpu_render(torch, merf, sc, cams, step=sc.step)
+    ref, st = oracle.render(sc, cams)
+    check(gpu, ref, st["fragile"], f"{size} thin {thin}", max_fragile=0.2)
+    assert np.array_equal(gpu, gpu_render(torch, merf, sc, cams, step=sc.step, skip="levels"))
