@@ -141,7 +141,7 @@ int64_t count_bricks(const merf_scene_desc *d) {
 
 // Offsets of the arrays inside a scene's single device allocation.
 struct Layout {
-    size_t bidx, bricks, planes, occ[kMaxLevels], dist, mlp, total;
+    size_t bidx, bricks, planes, occ[kMaxLevels], dist, mlp, mlp_frag, total;
 };
 
 // A scene without a grid gets a one-entry index (pointing at the zero brick);
@@ -161,6 +161,7 @@ Layout make_layout(const merf_scene_desc *d, int64_t nbricks) {
     const size_t rf = (size_t)d->occ_res[d->occ_levels - 1];
     o.dist = off; off = align_up(off + (rf <= (size_t)kOctMaxRes ? 8 : 1) * rf * rf * rf, 256);
     o.mlp = off; off = align_up(off + kMlpParams * sizeof(float), 256);
+    o.mlp_frag = off; off = align_up(off + kMlpFragWords * sizeof(uint32_t), 256);
     // a footprint at the planes' last texels reads a row and a texel pair past
     // them (with weight 0): the allocation reaches that far
     o.total = std::max(off, align_up(o.planes + 3 * R * R * kChannels + (R + 2) * kChannels, 256));
@@ -509,6 +510,9 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
     if (e == hipSuccess)
         e = launch_pack_bricks(stg(s_blocks), reinterpret_cast<const int32_t *>(stg(s_index)),
                                reinterpret_cast<const int32_t *>(stg(s_pos)), (int)nbricks, L, dev(o_bricks), stream);
+    if (e == hipSuccess)
+        e = launch_mlp_fragments(reinterpret_cast<const float *>(dev(o_mlp)), reinterpret_cast<uint32_t *>(dev(lay.mlp_frag)),
+                                 stream);
     if (e == hipSuccess) {
         OccLevels lv{};
         lv.n = desc->occ_levels;
@@ -548,6 +552,7 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
     ds.dist_oct_stride = octants ? (uint32_t)nf : 0u;
     ds.dist_cell = 4.0f / (float)rf;
     ds.mlp = reinterpret_cast<const float *>(dev(o_mlp));
+    ds.mlp_frag = reinterpret_cast<const uint32_t *>(dev(lay.mlp_frag));
     ds.L = L > 0 ? L : kBlock;            // stand-ins, see DevScene
     ds.R = R > 0 ? R : 2;
     ds.nbl = L > 0 ? nbl : 1;
@@ -664,6 +669,7 @@ int scene_from_image_on(const SceneImage &img, const void *host, hipStream_t str
     for (int l = 0; l < kMaxLevels; ++l) ds.occ[l] = at(img.ds.occ[l]);
     ds.dist = at(img.ds.dist);
     ds.mlp = reinterpret_cast<const float *>(at(img.ds.mlp));
+    ds.mlp_frag = reinterpret_cast<const uint32_t *>(at(img.ds.mlp_frag));
     {
         std::lock_guard<std::mutex> lk(g_mutex);
         g_live.insert(s);

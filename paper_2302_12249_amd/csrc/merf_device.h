@@ -17,6 +17,10 @@ constexpr int kMlpHidden = 16;
 constexpr int kMlpOut = 3;
 constexpr int kMlpParams = kMlpIn * kMlpHidden + kMlpHidden + kMlpHidden * kMlpHidden + kMlpHidden +
                            kMlpHidden * kMlpOut + kMlpOut;
+// Fragment table of the split fp32 MLP (merf_render.hip): a header, then 11
+// vectors of four words for each of 64 lanes.
+constexpr int kMlpHeader = 16;
+constexpr int kMlpFragWords = kMlpHeader + 11 * 64 * 4;
 constexpr int kTile = 8;                         // a wave renders an 8x8 pixel tile
 constexpr int kCamsPerLaunch = 16;               // cameras carried in one launch's arguments
 constexpr int kMaxDistRes = 1024;                // finest occupancy resolution (distance grid)
@@ -50,6 +54,8 @@ constexpr int kOrderMaxTiles = 1 << 17;
 //                nearest occupied cell, shared by all octants
 //                (dist_oct_stride = 0): the same forward cube with E = D.
 //   mlp          float32 W0[34][16] b0 W1[16][16] b1 W2[16][3] b2.
+//   mlp_frag     its weights split into float16 pairs, by lane of the matrix
+//                instructions.
 // A scene without a grid carries a stand-in grid (L = 8, one index entry
 // pointing at the zero brick); a scene without planes carries all-zero 2x2
 // stand-in planes (R = 2).  Stand-ins read code 0, and nsrc counts only the
@@ -62,6 +68,7 @@ struct DevScene {
     const uint8_t *occ[kMaxLevels];
     const uint8_t *dist;
     const float *mlp;
+    const uint32_t *mlp_frag;                    // kMlpFragWords, derived from mlp at upload
     int32_t L, R, nbl, occ_levels;
     int32_t occ_res[kMaxLevels];
     float occ_cell[kMaxLevels];                  // cell edge 4 / r of each level
@@ -192,6 +199,8 @@ hipError_t launch_gather_replay(const DevScene &sc, const uint32_t *rec, const i
 // the fp16-feature render path (deq_f16 with the scale the upload computes).
 hipError_t launch_dequant(const uint8_t *codes, int64_t n, float m, float a, int prec, void *out,
                           hipStream_t stream);
+// Builds the fragment table of an MLP.
+hipError_t launch_mlp_fragments(const float *mlp, uint32_t *frag, hipStream_t stream);
 // merf_ingest.hip: brick_pos[i] = bx | by << 10 | bz << 20 of brick slot i.
 hipError_t launch_pack_bricks(const uint8_t *blocks, const int32_t *block_index, const int32_t *brick_pos,
                               int nbricks, int L, uint8_t *bricks, hipStream_t stream);
