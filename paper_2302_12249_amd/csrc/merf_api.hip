@@ -4,12 +4,16 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <system_error>
+#include <thread>
 #include <unordered_set>
 #include <vector>
 
@@ -120,22 +124,29 @@ int validate_desc(const merf_scene_desc *d) {
 }
 
 // A brick is needed at block position b when any of the 8 blocks b + {0,1}^3
-// is stored.
+// is stored: the block mask ORed with its next cell along x, then y, then z
+// (whole rows at a time; testing the 8 blocks of each position, twice, took
+// longer than the device's share of an upload).
+std::vector<uint8_t> needed_bricks(const merf_scene_desc *d) {
+    const size_t n = (size_t)(d->grid_res / kBlock), rows = n * n, all = n * n * n;
+    std::vector<uint8_t> m(all);
+    for (size_t i = 0; i < all; ++i) m[i] = d->block_index[i] >= 0 ? 1 : 0;
+    for (size_t r = 0; r < rows; ++r) {
+        uint8_t *row = m.data() + r * n;
+        for (size_t x = 0; x + 1 < n; ++x) row[x] |= row[x + 1];
+    }
+    for (size_t r = 0; r < rows; ++r) {
+        if (r % n + 1 == n) continue;
+        uint8_t *row = m.data() + r * n;
+        for (size_t x = 0; x < n; ++x) row[x] |= row[x + n];
+    }
+    for (size_t i = 0; i + rows < all; ++i) m[i] |= m[i + rows];
+    return m;
+}
+
 int64_t count_bricks(const merf_scene_desc *d) {
-    const int nbl = d->grid_res / kBlock;
-    auto stored = [&](int bx, int by, int bz) {
-        return bx < nbl && by < nbl && bz < nbl && d->block_index[((size_t)bz * nbl + by) * nbl + bx] >= 0;
-    };
     int64_t n = 0;
-    for (int bz = 0; bz < nbl; ++bz)
-        for (int by = 0; by < nbl; ++by)
-            for (int bx = 0; bx < nbl; ++bx) {
-                bool need = false;
-                for (int dz = 0; dz < 2 && !need; ++dz)
-                    for (int dy = 0; dy < 2 && !need; ++dy)
-                        for (int dx = 0; dx < 2 && !need; ++dx) need = stored(bx + dx, by + dy, bz + dz);
-                n += need ? 1 : 0;
-            }
+    for (uint8_t v : needed_bricks(d)) n += v;
     return n;
 }
 
@@ -174,22 +185,15 @@ Layout make_layout(const merf_scene_desc *d, int64_t nbricks) {
 // The host only assigns the slots; the device packs the voxels.
 void assign_bricks(const merf_scene_desc *d, std::vector<int32_t> &bidx, std::vector<int32_t> &pos) {
     const int nbl = d->grid_res / kBlock;
-    auto stored = [&](int bx, int by, int bz) {
-        return bx < nbl && by < nbl && bz < nbl && d->block_index[((size_t)bz * nbl + by) * nbl + bx] >= 0;
-    };
-    bidx.assign((size_t)nbl * nbl * nbl, -1);
+    const std::vector<uint8_t> need = needed_bricks(d);
+    bidx.assign(need.size(), 0);
     pos.clear();
+    size_t i = 0;
     for (int bz = 0; bz < nbl; ++bz)
         for (int by = 0; by < nbl; ++by)
-            for (int bx = 0; bx < nbl; ++bx) {
-                bool need = false;
-                for (int dz = 0; dz < 2 && !need; ++dz)
-                    for (int dy = 0; dy < 2 && !need; ++dy)
-                        for (int dx = 0; dx < 2 && !need; ++dx) need = stored(bx + dx, by + dy, bz + dz);
-                if (need) {
-                    bidx[((size_t)bz * nbl + by) * nbl + bx] = (int32_t)pos.size();
-                    pos.push_back(bx | (by << 10) | (bz << 20));
-                }
+            for (int bx = 0; bx < nbl; ++bx, ++i) {
+                bidx[i] = need[i] ? (int32_t)pos.size() : -1;
+                if (need[i]) pos.push_back(bx | (by << 10) | (bz << 20));
             }
     const int32_t zero = (int32_t)pos.size();
     for (int32_t &b : bidx)
@@ -430,6 +434,238 @@ hipError_t dev_free(void *p, bool ordered, hipStream_t stream) {
     return ordered ? hipFreeAsync(p, stream) : hipFree(p);
 }
 
+// What uploads and the empty-space entry points use for a moment and the
+// library keeps for the next: device scratch (a memory pool per device that
+// holds on to at most kScratchKept bytes) and pinned host buffers (CopyRing).
+// Allocating and freeing them each time took 0.38 ms of an upload and half of
+// a 256^3 octant grid's 0.58 ms.  Both are given back when the last scene is
+// freed, unless they were used within the last second (scenes opened and
+// closed in turn), and the scratch also when a device allocation fails.
+constexpr size_t kScratchKept = (size_t)256 << 20;
+constexpr int kScratchDevices = 16;
+constexpr auto kKeepAfterUse = std::chrono::seconds(1);
+using Clock = std::chrono::steady_clock;
+
+std::mutex g_scratch_mutex;
+hipMemPool_t g_scratch_pool[kScratchDevices] = {};   // created on first use
+Clock::time_point g_scratch_used{};
+
+// The scratch pool of the current device, or null.
+hipMemPool_t scratch_pool() {
+    int device = -1;
+    if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= kScratchDevices) return nullptr;
+    std::lock_guard<std::mutex> lk(g_scratch_mutex);
+    if (!g_scratch_pool[device]) {
+        hipMemPoolProps props{};
+        props.allocType = hipMemAllocationTypePinned;
+        props.location.type = hipMemLocationTypeDevice;
+        props.location.id = device;
+        hipMemPool_t pool = nullptr;
+        uint64_t kept = kScratchKept;
+        if (hipMemPoolCreate(&pool, &props) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        if (hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &kept) != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipMemPoolDestroy(pool);
+            return nullptr;
+        }
+        g_scratch_pool[device] = pool;
+    }
+    g_scratch_used = Clock::now();
+    return g_scratch_pool[device];
+}
+
+void trim_scratch() {
+    std::lock_guard<std::mutex> lk(g_scratch_mutex);
+    for (hipMemPool_t pool : g_scratch_pool)
+        if (pool) (void)hipMemPoolTrimTo(pool, 0);
+}
+
+// Scratch of n bytes, ordered on stream; from the pool up to its size, else
+// (and on a stream that is capturing) allocated and freed plainly.
+struct Scratch {
+    void *p = nullptr;
+    bool pooled = false;
+    hipError_t alloc(size_t n, hipStream_t stream) {
+        hipMemPool_t pool = n <= kScratchKept && !capturing(stream) ? scratch_pool() : nullptr;
+        if (pool && hipMallocFromPoolAsync(&p, n, pool, stream) == hipSuccess && p) {
+            pooled = true;
+            return hipSuccess;
+        }
+        if (pool) (void)hipGetLastError();
+        return plain(n);
+    }
+    hipError_t plain(size_t n) {
+        hipError_t e = hipMalloc(&p, n);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            trim_scratch();
+            e = hipMalloc(&p, n);
+        }
+        return e;
+    }
+    void free(hipStream_t stream) {
+        if (p) (void)(pooled ? hipFreeAsync(p, stream) : hipFree(p));
+        p = nullptr;
+    }
+};
+
+// Host-to-device copies of an upload from ordinary (pageable) memory.  The
+// runtime moves such memory at 20 to 29 GB/s, which was most of the time it
+// takes to open a full scene (155 MB); here kCopyThreads threads fill pinned
+// chunks, two each, whose copies run meanwhile on a stream of the thread's own:
+// 50 GB/s, near the 55 of a source that is pinned itself (38 with one stream
+// for all threads; 6 threads and chunks of 1 or 4 MB gain nothing).
+struct Copy {
+    uint8_t *dst;
+    const void *src;
+    size_t n;
+};
+constexpr int kCopyThreads = 4;
+constexpr int kChunksEach = 2;
+constexpr size_t kChunk = (size_t)2 << 20;
+constexpr size_t kStagedMin = (size_t)4 << 20;      // of an upload: less gains nothing
+
+struct CopyRing {
+    struct Lane {
+        hipStream_t stream = nullptr;
+        uint8_t *chunk[kChunksEach] = {};
+        hipEvent_t done[kChunksEach] = {};
+    };
+    std::mutex busy;                                // held during a staged copy
+    int device = -1;                                // of the streams and events; -1: nothing allocated
+    Lane lane[kCopyThreads];
+    Clock::time_point used{};
+
+    void release() {                                // (no copy from a chunk is in flight)
+        for (Lane &l : lane) {
+            for (int k = 0; k < kChunksEach; ++k) {
+                if (l.chunk[k]) (void)hipHostFree(l.chunk[k]);
+                if (l.done[k]) (void)hipEventDestroy(l.done[k]);
+            }
+            if (l.stream) (void)hipStreamDestroy(l.stream);
+            l = Lane{};
+        }
+        device = -1;
+    }
+    bool prepare(int dev) {
+        if (device == dev) return true;
+        release();
+        for (Lane &l : lane) {
+            bool ok = hipStreamCreateWithFlags(&l.stream, hipStreamNonBlocking) == hipSuccess;
+            for (int k = 0; ok && k < kChunksEach; ++k)
+                ok = hipHostMalloc(reinterpret_cast<void **>(&l.chunk[k]), kChunk, hipHostMallocPortable) ==
+                         hipSuccess &&
+                     hipEventCreateWithFlags(&l.done[k], hipEventDisableTiming) == hipSuccess;
+            if (!ok) {
+                (void)hipGetLastError();
+                release();
+                return false;
+            }
+        }
+        device = dev;
+        return true;
+    }
+    // Copies the whole list; all of it is done when this returns.
+    hipError_t run(const std::vector<Copy> &list) {
+        std::vector<Copy> pieces;
+        for (const Copy &c : list)
+            for (size_t at = 0; at < c.n; at += kChunk)
+                pieces.push_back({c.dst + at, static_cast<const uint8_t *>(c.src) + at, std::min(kChunk, c.n - at)});
+        std::atomic<size_t> next{0};
+        std::atomic<int> error{(int)hipSuccess};
+        auto work = [&](int t) {
+            Lane &l = lane[t];
+            hipError_t e = hipSetDevice(device);
+            bool filled[kChunksEach] = {};
+            for (int k = 0; e == hipSuccess && error.load() == (int)hipSuccess; k = (k + 1) % kChunksEach) {
+                const size_t i = next.fetch_add(1);
+                if (i >= pieces.size()) break;
+                if (filled[k]) e = hipEventSynchronize(l.done[k]);
+                if (e != hipSuccess) break;
+                std::memcpy(l.chunk[k], pieces[i].src, pieces[i].n);
+                e = hipMemcpyAsync(pieces[i].dst, l.chunk[k], pieces[i].n, hipMemcpyHostToDevice, l.stream);
+                if (e == hipSuccess) e = hipEventRecord(l.done[k], l.stream);
+                filled[k] = true;
+            }
+            const hipError_t w = hipStreamSynchronize(l.stream);    // also when a copy before it failed
+            if (e == hipSuccess) e = w;
+            if (e != hipSuccess) error.store((int)e);
+        };
+        std::vector<std::thread> threads;
+        threads.reserve(kCopyThreads);
+        const int want = (int)std::min<size_t>(kCopyThreads, pieces.size());
+        try {
+            for (int t = 1; t < want; ++t) threads.emplace_back(work, t);
+        } catch (const std::system_error &) {       // no more threads: those there are do it
+        }
+        work(0);
+        for (std::thread &t : threads) t.join();
+        used = Clock::now();
+        return (hipError_t)error.load();
+    }
+};
+// never destroyed: at process exit the runtime may already be gone
+CopyRing &copy_ring() {
+    static CopyRing *ring = new CopyRing();
+    return *ring;
+}
+
+// Whether p is ordinary host memory: not known to the runtime.
+bool pageable(const void *p) {
+    hipPointerAttribute_t at{};
+    const hipError_t e = hipPointerGetAttributes(&at, p);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();                    // (unknown to older runtimes)
+        return e == hipErrorInvalidValue;
+    }
+    return at.type == hipMemoryTypeUnregistered;
+}
+
+// The copies of an upload, on stream (ordered) or synchronously.  Sources may
+// be host or device memory (e.g. a pyramid built by merf_occupancy_pyramid).
+// The staged ones run on streams of their own and are done when this returns:
+// no work that touches the destinations may be pending.
+hipError_t upload_copies(const std::vector<Copy> &copies, bool ordered, hipStream_t stream) {
+    std::vector<Copy> staged, plain;
+    size_t bytes = 0;
+    for (const Copy &c : copies) {
+        if (c.n == 0) continue;
+        const bool st = pageable(c.src);
+        (st ? staged : plain).push_back(c);
+        if (st) bytes += c.n;
+    }
+    CopyRing &ring = copy_ring();
+    std::unique_lock<std::mutex> busy(ring.busy, std::try_to_lock);      // one upload at a time stages
+    int device = -1;
+    if (bytes < kStagedMin || !busy.owns_lock() || hipGetDevice(&device) != hipSuccess || !ring.prepare(device)) {
+        plain.insert(plain.end(), staged.begin(), staged.end());
+        staged.clear();
+    }
+    for (const Copy &c : plain) {
+        const hipError_t e = ordered ? hipMemcpyAsync(c.dst, c.src, c.n, hipMemcpyDefault, stream)
+                                     : hipMemcpy(c.dst, c.src, c.n, hipMemcpyDefault);
+        if (e != hipSuccess) return e;
+    }
+    return staged.empty() ? hipSuccess : ring.run(staged);
+}
+
+// After the last scene is freed: what was not used lately goes back.
+void release_idle() {
+    const Clock::time_point now = Clock::now();
+    bool idle;
+    {
+        std::lock_guard<std::mutex> lk(g_scratch_mutex);
+        idle = now - g_scratch_used > kKeepAfterUse;
+    }
+    if (idle) trim_scratch();
+    CopyRing &ring = copy_ring();
+    std::unique_lock<std::mutex> busy(ring.busy, std::try_to_lock);
+    if (busy.owns_lock() && now - ring.used > kKeepAfterUse) ring.release();
+}
+
 // merf_scene_upload (ordered = false: null stream, plain allocation) and
 // scene_upload_on (ordered = true: everything on stream).
 int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hipStream_t stream) {
@@ -440,11 +676,11 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
     if (rc) return rc;
     if (!ordered) stream = nullptr;
 
-    const int64_t nbricks = count_bricks(desc);
-    if ((nbricks + 1) * (int64_t)kBrickBytes >= (int64_t)1 << 31)
-        return fail(MERF_E_INVALID, "%lld bricks exceed the 2 GiB addressed by 32-bit offsets", (long long)nbricks);
     std::vector<int32_t> bidx, bpos;
     assign_bricks(desc, bidx, bpos);
+    const int64_t nbricks = (int64_t)bpos.size();
+    if ((nbricks + 1) * (int64_t)kBrickBytes >= (int64_t)1 << 31)
+        return fail(MERF_E_INVALID, "%lld bricks exceed the 2 GiB addressed by 32-bit offsets", (long long)nbricks);
     const int L = desc->grid_res, R = desc->plane_res, nbl = L / kBlock;
     const Layout lay = make_layout(desc, nbricks);
     const size_t o_bidx = lay.bidx, o_bricks = lay.bricks, o_planes = lay.planes, o_mlp = lay.mlp, total = lay.total;
@@ -472,12 +708,21 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
     // scratch of the empty-space grid: the octants', or two byte grids
     const size_t s_dist1 = s_dist0 + align_up(nf, 256),
                  staging = octants ? s_dist0 + octant_scratch_bytes((int)rf) : s_dist1 + align_up(nf, 256);
-    void *base = nullptr, *stage = nullptr;
+    void *base = nullptr;
+    Scratch scratch;
     hipError_t e = dev_alloc(&base, total, ordered, stream);
-    if (e == hipSuccess) e = dev_alloc(&stage, staging, ordered, stream);
-    if (e == hipSuccess && ordered) e = hipStreamSynchronize(stream);   // allocation failures surface here
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        trim_scratch();
+        e = dev_alloc(&base, total, ordered, stream);
+    }
+    if (e == hipSuccess) e = scratch.alloc(staging, stream);
+    // allocation failures surface here; and the copies use streams of their own
+    if (e == hipSuccess && (ordered || scratch.pooled)) e = hipStreamSynchronize(stream);
+    void *stage = scratch.p;
     if (e != hipSuccess || !base || !stage) {
         (void)hipGetLastError();
+        scratch.free(stream);
         if (base) (void)dev_free(base, ordered, stream);
         if (base && ordered) (void)hipStreamSynchronize(stream);
         release();
@@ -485,7 +730,6 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
     }
     auto dev = [&](size_t o) { return static_cast<uint8_t *>(base) + o; };
     auto stg = [&](size_t o) { return static_cast<uint8_t *>(stage) + o; };
-    struct Copy { uint8_t *dst; const void *src; size_t n; };
     std::vector<Copy> copies = {
         {dev(o_bidx), bidx.data(), bidx.size() * sizeof(int32_t)},
         {dev(o_planes), desc->planes, (size_t)3 * R * R * kChannels},
@@ -498,14 +742,7 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
         size_t r = (size_t)desc->occ_res[l];
         copies.push_back({dev(o_occ[l]), desc->occ[l], r * r * r});
     }
-    for (const Copy &c : copies) {
-        if (c.n == 0) continue;
-        // hipMemcpyDefault: blocks, planes, occupancy levels and MLP may be
-        // host or device memory (e.g. a pyramid built by merf_occupancy_pyramid)
-        e = ordered ? hipMemcpyAsync(c.dst, c.src, c.n, hipMemcpyDefault, stream)
-                    : hipMemcpy(c.dst, c.src, c.n, hipMemcpyDefault);
-        if (e != hipSuccess) break;
-    }
+    e = upload_copies(copies, ordered, stream);
     if (e == hipSuccess && R == 0) e = hipMemsetAsync(dev(o_planes), 0, (size_t)3 * 2 * 2 * kChannels, stream);
     if (e == hipSuccess)
         e = launch_pack_bricks(stg(s_blocks), reinterpret_cast<const int32_t *>(stg(s_index)),
@@ -524,7 +761,7 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
                     : launch_distance_grid(lv, stg(s_dist0), stg(s_dist1), dev(lay.dist), stream);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    (void)dev_free(stage, ordered, stream);
+    scratch.free(stream);
     if (e != hipSuccess) {
         (void)dev_free(base, ordered, stream);
         if (ordered) (void)hipStreamSynchronize(stream);
@@ -601,6 +838,11 @@ bool unregister(merf_scene_t s) {
     g_live.erase(s);
     g_in_use -= s->dev_bytes;
     return true;
+}
+
+bool no_scene_left() {
+    std::lock_guard<std::mutex> lk(g_mutex);
+    return g_live.empty();
 }
 
 }  // namespace
@@ -684,6 +926,7 @@ int scene_release_on(merf_scene_t s, hipStream_t stream) {
     const hipError_t e = dev_free(s->dev_base, s->ordered, stream);
     s->magic = 0;
     delete s;
+    if (no_scene_left()) release_idle();
     if (e != hipSuccess) return hip_fail(e, "scene release");
     return MERF_OK;
 }
@@ -702,6 +945,7 @@ int merf_free(merf_scene_t s) {
     if (e2 == hipSuccess && s->ordered) e2 = hipStreamSynchronize(nullptr);
     s->magic = 0;
     delete s;
+    if (no_scene_left()) release_idle();
     if (e1 != hipSuccess) return hip_fail(e1, "hipDeviceSynchronize (merf_free)");
     if (e2 != hipSuccess) return hip_fail(e2, "hipFree (merf_free)");
     return MERF_OK;
@@ -910,17 +1154,17 @@ int merf_distance_grid(const uint8_t *const *occ_dev, const int32_t *res, int32_
     int rc = occ_levels_arg(occ_dev, res, n_levels, out_dev, lv);
     if (rc) return rc;
     const size_t r = (size_t)res[n_levels - 1], n = r * r * r;
-    void *tmp = nullptr;
-    hipError_t e = hipMalloc(&tmp, 2 * align_up(n, 256));
-    if (e != hipSuccess || !tmp) {
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    Scratch tmp;
+    hipError_t e = tmp.alloc(2 * align_up(n, 256), stream);
+    if (e != hipSuccess || !tmp.p) {
         (void)hipGetLastError();
         return fail(MERF_E_OOM, "hipMalloc of %zu scratch bytes failed", 2 * align_up(n, 256));
     }
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    uint8_t *t0 = static_cast<uint8_t *>(tmp), *t1 = t0 + align_up(n, 256);
+    uint8_t *t0 = static_cast<uint8_t *>(tmp.p), *t1 = t0 + align_up(n, 256);
     e = launch_distance_grid(lv, t0, t1, out_dev, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    (void)hipFree(tmp);
+    tmp.free(stream);
     if (e != hipSuccess) return hip_fail(e, "distance grid");
     return MERF_OK;
 }
@@ -932,16 +1176,16 @@ int merf_octant_extent_grid(const uint8_t *const *occ_dev, const int32_t *res, i
     int rc = occ_levels_arg(occ_dev, res, n_levels, out_dev, lv);
     if (rc) return rc;
     const size_t bytes = octant_scratch_bytes(res[n_levels - 1]);
-    void *tmp = nullptr;
-    hipError_t e = hipMalloc(&tmp, bytes);
-    if (e != hipSuccess || !tmp) {
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    Scratch tmp;
+    hipError_t e = tmp.alloc(bytes, stream);
+    if (e != hipSuccess || !tmp.p) {
         (void)hipGetLastError();
         return fail(MERF_E_OOM, "hipMalloc of %zu scratch bytes failed", bytes);
     }
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    e = launch_octant_extents(lv, static_cast<uint8_t *>(tmp), out_dev, stream);
+    e = launch_octant_extents(lv, static_cast<uint8_t *>(tmp.p), out_dev, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    (void)hipFree(tmp);
+    tmp.free(stream);
     if (e != hipSuccess) return hip_fail(e, "octant extent grid");
     return MERF_OK;
 }
