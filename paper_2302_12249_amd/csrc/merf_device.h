@@ -231,11 +231,11 @@ hipError_t launch_distance_grid(const OccLevels &lv, uint8_t *tmp0, uint8_t *tmp
                                 hipStream_t stream);
 // Forward empty extents of DevScene::dist in its eight-octant form (scratch:
 // octant_scratch_bytes(r_f), 16-byte aligned; out: 8 r_f^3 bytes).
-// Grids of scratch, padded rows of x: runs of empty cells along each axis and
-// sign, and empty squares of the xy and xz planes by sign of x (bit 0) and of
-// the other axis (bit 1).
+// Grids of scratch, padded rows of x: runs of empty cells along x by sign, and
+// empty squares of the xy and xz planes by sign of x (bit 0) and of the other
+// axis (bit 1).
 struct OctantScratch {
-    uint8_t *gx[2], *gy[2], *gz[2], *fxy[4], *fxz[4];
+    uint8_t *gx[2], *fxy[4], *fxz[4];
     int32_t r, rp;                               // cells a side, cells of a padded row
     bool single;                                 // one octant at a time
 };

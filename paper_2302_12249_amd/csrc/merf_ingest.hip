@@ -179,16 +179,20 @@ __global__ void k_dist_axis(const uint8_t *__restrict__ in, uint8_t *__restrict_
 
 // Forward empty extents.  E(c) of octant (sx, sy, sz) is the edge of the
 // largest empty cube with a corner at cell c that extends the octant's way
-// (cells outside the grid are empty; at most 255).  Growing from the cube one
-// cell further along the diagonal, only the three faces at c are new:
-//   E(c)   = min(E(c + (sx, sy, sz)) + 1, Fxy(c), Fxz(c), Fyz(c)),
-// with Fxy the largest empty square at c in its z plane, and in the same way
-//   Fxy(c) = min(Fxy(c + (sx, sy, 0)) + 1, Gx(c), Gy(c)),
-// with Gx the run of empty cells from c along x (0 at an occupied cell).  So
-// four kernels take a cell a constant number of steps each and are bound by
-// their traffic: 278 us for the eight grids of 256^3 cells (3.6 TB/s), 109 us
-// for 128^3.  (A bisection of each extent in a table of prefix sums takes 64
-// lookups per cell and octant: 4.25 ms and 0.64 ms.)
+// (cells outside the grid are empty; at most 255).  A cube of edge m at c is
+// its face in c's z plane, its face in c's y plane and the two cubes of edge
+// m - 1 one step along (sy, sz) from c, with and without a step along sx:
+//   E(c)   = min(Fxy(c), Fxz(c), 1 + E(c + (0, sy, sz)), 1 + E(c + (sx, sy, sz))),
+// with Fxy the largest empty square at c in its z plane, which in the same way
+// is a row and two squares,
+//   Fxy(c) = min(Gx(c), 1 + Fxy(c + (0, sy, 0)), 1 + Fxy(c + (sx, sy, 0))),
+// Fxz likewise, and Gx the run of empty cells from c along x (0 at an occupied
+// cell).  So three kernels take a cell a constant number of steps each and are
+// bound by their traffic, 43 bytes a cell for the eight grids: 167 us for 256^3
+// cells (4.3 TB/s; a plain copy reaches 5.2).
+// (Growing from the cube on the diagonal needs all three faces and the runs
+// along y and z, 63 bytes a cell: 278 us.  A bisection of each extent in a
+// table of prefix sums takes 64 lookups per cell and octant: 4.25 ms.)
 // Bytes are held as pairs of 16-bit lanes (the even and the odd cells of a
 // word), so packed 16-bit instructions do two cells at a time, and a lane
 // group holds a whole row of x in registers: a step along the diagonal is then
@@ -297,14 +301,22 @@ __device__ __forceinline__ Cells<N> shift_x(const Cells<N> &a, bool neg, bool la
     return c;
 }
 
+// What the cubes (or squares) of the row before allow: 1 + the smaller of each
+// cell's and of the next one's along x.
+template <int N>
+__device__ __forceinline__ Cells<N> grow(const Cells<N> &a, bool neg, bool last) {
+    return plus_one<N>(min_cells<N>(a, shift_x<N>(a, neg, last)));
+}
+
 // Rows of a wave: a row takes rp / N lanes, a wave as many rows as fit.
 template <int N>
 struct Lanes {
     int per_row, i, row;            // lanes of a row, this lane's place in it, the row (in the wave)
     __device__ __forceinline__ explicit Lanes(int rp) {
+        const int lane = (int)threadIdx.x & 63;
         per_row = rp / N;
-        row = (int)threadIdx.x / per_row;
-        i = (int)threadIdx.x - row * per_row;
+        row = lane / per_row;
+        i = lane - row * per_row;
         if (row >= 64 / per_row) row = 1 << 20;               // a lane left over
     }
 };
@@ -312,12 +324,15 @@ struct Lanes {
 // Step 1, a lane group per row of x: the cells occupied at every level and the
 // runs of empty cells along +x (gx[0]) and -x (gx[1]).  The next occupied cell
 // past a lane's own comes from the nearest lane that has one (a ballot and one
-// shuffle each way).
+// shuffle each way).  Bound by its instructions, most of them once a lane: with
+// 16 cells a lane it takes 27 us for 256^3 cells, with 4 it takes 37.
+constexpr int kRunWaves = 4;
 template <int N>
-__global__ __launch_bounds__(64) void k_runs_x(const OccLevels lv, const OctantScratch sc) {
+__global__ __launch_bounds__(64 * kRunWaves) void k_runs_x(const OccLevels lv, const OctantScratch sc) {
     const int r = sc.r, rp = sc.rp;
     const Lanes<N> ln(rp);
-    const uint32_t row = blockIdx.x * (uint32_t)(64 / ln.per_row) + (uint32_t)ln.row;
+    const uint32_t wave = blockIdx.x * (uint32_t)kRunWaves + threadIdx.x / 64u;
+    const uint32_t row = wave * (uint32_t)(64 / ln.per_row) + (uint32_t)ln.row;
     const bool live = row < (uint32_t)r * (uint32_t)r;
     const int y = (int)(row % (uint32_t)r), z = (int)(row / (uint32_t)r), x0 = ln.i * N;
     uint32_t occ = 0u;                                        // bit k: cell x0 + k
@@ -341,13 +356,22 @@ __global__ __launch_bounds__(64) void k_runs_x(const OccLevels lv, const OctantS
         for (int l = 0; l + 1 < lv.n && occ; ++l) {
             const int rl = lv.res[l], q = r / rl;
             const uint8_t *o = lv.occ[l] + ((size_t)(z / q) * rl + y / q) * rl;
+            int cell = x0 / q, left = q - (x0 - cell * q);    // cells of q left in the coarse one
+            uint8_t c[N];                                     // (loads in flight together; none past the row)
 #pragma unroll
-            for (int k = 0; k < N; ++k)
-                if ((occ >> k & 1u) && o[(x0 + k) / q] == 0) occ &= ~(1u << k);
+            for (int k = 0; k < N; ++k) {
+                c[k] = o[min(cell, rl - 1)];
+                if (--left == 0) {
+                    ++cell;
+                    left = q;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < N; ++k) occ &= c[k] ? ~0u : ~(1u << k);
         }
     }
     const uint64_t have = __builtin_amdgcn_ballot_w64(occ != 0);
-    const int lane = (int)threadIdx.x, first = lane - ln.i;   // first lane of the row
+    const int lane = (int)threadIdx.x & 63, first = lane - ln.i;   // first lane of the row
     const uint64_t in_row = (ln.per_row == 64 ? ~0ull : (1ull << ln.per_row) - 1) << (first & 63);
     const uint64_t after = lane < 63 ? have & in_row & (~0ull << (lane + 1)) : 0ull;
     const uint64_t before = have & in_row & ((1ull << lane) - 1);
@@ -378,25 +402,23 @@ __global__ __launch_bounds__(64) void k_runs_x(const OccLevels lv, const OctantS
     if (sc.gx[1]) put(sc.gx[1]);
 }
 
-// Step 2: for each sign of x (bit 0 of the combination) and of the axis
-// marched along (bit 1; y with kAlongZ false, else z), a lane group per line
-// of rows: the runs G along that axis and the squares F of the plane it spans
-// with x.
+// Step 2: the squares of the planes that x spans with y (blockIdx.z = 0) and
+// with z (1), for each sign of x (bit 0 of the combination) and of the other
+// axis (bit 1): a lane group per line of rows marches along that axis, from its
+// far end.
 constexpr int kRowsAhead = 8;
-template <int N, bool kAlongZ>
-__global__ __launch_bounds__(64) void k_squares_x(const OctantScratch sc, int first_combo) {
-    const int r = sc.r, rp = sc.rp, combo = first_combo + (int)blockIdx.y, sx = combo & 1, sa = combo >> 1;
+template <int N>
+__global__ __launch_bounds__(64) void k_squares_x(const OctantScratch sc, int first_xy, int first_xz) {
+    const bool along_z = blockIdx.z != 0;
+    const int r = sc.r, rp = sc.rp, combo = (along_z ? first_xz : first_xy) + (int)blockIdx.y, sx = combo & 1;
     const Lanes<N> ln(rp);
     const int line = (int)blockIdx.x * (64 / ln.per_row) + ln.row;
-    const bool live = line < r, last = ln.i == (sx ? 0 : ln.per_row - 1);
-    // row s of the march: from the far end of the axis towards this side
-    const int64_t stride = (int64_t)rp * (kAlongZ ? r : 1);
-    const int64_t step = sa ? stride : -stride;
-    int64_t at = (live ? (int64_t)line * rp * (kAlongZ ? 1 : r) : 0) + ln.i % ln.per_row * N + (sa ? 0 : (int64_t)(r - 1) * stride);
+    const bool live = line < r, last = ln.i == (sx ? 0 : ln.per_row - 1), up = combo >> 1;
+    const int64_t stride = (int64_t)rp * (along_z ? r : 1), step = up ? stride : -stride;
+    int64_t at = (live ? (int64_t)line * rp * (along_z ? 1 : r) : 0) + ln.i % ln.per_row * N + (up ? 0 : (int64_t)(r - 1) * stride);
     const uint8_t *gx = sc.gx[sx];
-    uint8_t *ga = (kAlongZ ? sc.gz : sc.gy)[sa], *f = (kAlongZ ? sc.fxz : sc.fxy)[combo];
-    const bool runs = sc.single || sx == 0;                   // one of the two combinations of sa stores G
-    Cells<N> run = fill_cells<N>(255), sq = fill_cells<N>(255);
+    uint8_t *f = (along_z ? sc.fxz : sc.fxy)[combo];
+    Cells<N> sq = fill_cells<N>(255);
     Row<N> ahead[kRowsAhead];
 #pragma unroll
     for (int u = 0; u < kRowsAhead; ++u) ahead[u] = load_row<N>(gx + at + (int64_t)min(u, r - 1) * step);
@@ -410,38 +432,26 @@ __global__ __launch_bounds__(64) void k_squares_x(const OctantScratch sc, int fi
 #pragma unroll
         for (int u = 0; u < kRowsAhead; ++u) {
             if (s0 + u < r) {
-                const Cells<N> g = unpack<N>(cur[u]);
-#pragma unroll
-                for (int i = 0; i < N / 4; ++i) {             // 0 where occupied, else one more
-                    const u16x2 ke = splat(0) - __builtin_elementwise_min(g.e[i], splat(1));
-                    const u16x2 ko = splat(0) - __builtin_elementwise_min(g.o[i], splat(1));
-                    run.e[i] = __builtin_elementwise_min(run.e[i] + splat(1), splat(255)) & ke;
-                    run.o[i] = __builtin_elementwise_min(run.o[i] + splat(1), splat(255)) & ko;
-                }
-                sq = min_cells<N>(plus_one<N>(shift_x<N>(sq, sx != 0, last)), min_cells<N>(g, run));
-                if (live) {
-                    store_row<N>(f + at, pack<N>(sq));
-                    if (runs) store_row<N>(ga + at, pack<N>(run));
-                }
+                sq = min_cells<N>(unpack<N>(cur[u]), grow<N>(sq, sx != 0, last));
+                if (live) store_row<N>(f + at, pack<N>(sq));
                 at += step;
             }
         }
     }
 }
 
-// Step 3: for each octant, a lane group per diagonal of rows in (y, z): the
-// squares of the yz plane and the extents.  Line d starts at row y = d of the
+// Step 3: for each octant, a lane group per diagonal of rows in (y, z).  Line d starts at row y = d of the
 // far z; where y leaves the grid the line goes on as another diagonal, from
 // the far y.
 template <int N>
 __global__ __launch_bounds__(64) void k_extents(const OctantScratch sc, int first_octant, bool words, uint8_t *__restrict__ out) {
-    constexpr int kAhead = N == 16 ? 2 : 4;
+    constexpr int kAhead = N == 16 ? 4 : 8;
     const int r = sc.r, rp = sc.rp, o = first_octant + (int)blockIdx.y, sx = o & 1, sy = o >> 1 & 1, sz = o >> 2;
     const Lanes<N> ln(rp);
     const int line = (int)blockIdx.x * (64 / ln.per_row) + ln.row;
     const bool live = line < r, last = ln.i == (sx ? 0 : ln.per_row - 1);
     const int x0 = ln.i % ln.per_row * N, d = live ? line : 0;
-    const uint8_t *gy = sc.gy[sy], *gz = sc.gz[sz], *fxy = sc.fxy[sx | sy << 1], *fxz = sc.fxz[sx | sz << 1];
+    const uint8_t *fxy = sc.fxy[sx | sy << 1], *fxz = sc.fxz[sx | sz << 1];
     uint8_t *to = out + (sc.single ? 0 : (size_t)o * r * r * r);
     // rows (y, z) of step s: z from the far end, y from d the same way
     auto y_of = [&](int s) {
@@ -449,22 +459,21 @@ __global__ __launch_bounds__(64) void k_extents(const OctantScratch sc, int firs
         return y >= r ? y - r : y < 0 ? y + r : y;
     };
     auto row_of = [&](int s) { return (uint32_t)((sz ? s : r - 1 - s) * r + y_of(s)); };
-    Cells<N> sq = fill_cells<N>(255), e = fill_cells<N>(255);
-    Row<N> a0[kAhead], a1[kAhead], a2[kAhead], a3[kAhead];
+    Cells<N> e = fill_cells<N>(255);
+    Row<N> a0[kAhead], a1[kAhead];
     auto fetch = [&](int u, int s) {
         const size_t at = (size_t)row_of(min(s, r - 1)) * rp + x0;
-        a0[u] = load_row<N>(gy + at);
-        a1[u] = load_row<N>(gz + at);
-        a2[u] = load_row<N>(fxy + at);
-        a3[u] = load_row<N>(fxz + at);
+        a0[u] = load_row<N>(fxy + at);
+        a1[u] = load_row<N>(fxz + at);
     };
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) fetch(u, u);
     for (int s0 = 0; s0 < r; s0 += kAhead) {
-        Row<N> b0[kAhead], b1[kAhead], b2[kAhead], b3[kAhead];
+        Row<N> b0[kAhead], b1[kAhead];
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
-            b0[u] = a0[u]; b1[u] = a1[u]; b2[u] = a2[u]; b3[u] = a3[u];
+            b0[u] = a0[u];
+            b1[u] = a1[u];
         }
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) fetch(u, s0 + kAhead + u);
@@ -472,13 +481,8 @@ __global__ __launch_bounds__(64) void k_extents(const OctantScratch sc, int firs
         for (int u = 0; u < kAhead; ++u) {
             const int s = s0 + u;
             if (s < r) {
-                if (y_of(s) == (sy ? 0 : r - 1)) {            // the row before it is outside
-                    sq = fill_cells<N>(255);
-                    e = fill_cells<N>(255);
-                }
-                sq = min_cells<N>(plus_one<N>(sq), min_cells<N>(unpack<N>(b0[u]), unpack<N>(b1[u])));
-                e = min_cells<N>(plus_one<N>(shift_x<N>(e, sx != 0, last)),
-                                 min_cells<N>(sq, min_cells<N>(unpack<N>(b2[u]), unpack<N>(b3[u]))));
+                if (y_of(s) == (sy ? 0 : r - 1)) e = fill_cells<N>(255);      // the row before it is outside
+                e = min_cells<N>(grow<N>(e, sx != 0, last), min_cells<N>(unpack<N>(b0[u]), unpack<N>(b1[u])));
                 const Row<N> w = pack<N>(e);
                 if (live) {
                     uint8_t *p = to + (size_t)row_of(s) * r + x0;
@@ -500,12 +504,12 @@ __global__ __launch_bounds__(64) void k_extents(const OctantScratch sc, int firs
 
 }  // namespace
 
-// The eight octants together need 14 padded grids of scratch; above
+// The eight octants together need 10 padded grids of scratch; above
 // kOctMaxRes (which no upload needs) they are built one after another from
-// five, the scratch that a table of prefix sums took.
+// three.
 size_t octant_scratch_bytes(int r) {
     const size_t grid = (size_t)r * r * ((size_t)(r + 15) / 16 * 16);
-    return grid * (r <= kOctMaxRes ? 14 : 5);
+    return grid * (r <= kOctMaxRes ? 10 : 3);
 }
 
 namespace {
@@ -518,7 +522,8 @@ hipError_t octant_extents(const OccLevels &lv, uint8_t *scratch, uint8_t *out, h
     sc.single = sc.r > kOctMaxRes;
     const size_t r = (size_t)sc.r, n = r * r * r, grid = r * r * (size_t)sc.rp;
     const unsigned rows = 64u / (unsigned)(sc.rp / N);        // rows of a wave
-    const unsigned row_blocks = (unsigned)((r * r + rows - 1) / rows), line_blocks = (unsigned)((r + rows - 1) / rows);
+    const size_t run_rows = 64u / (unsigned)(sc.rp / 16) * kRunWaves;         // rows of a workgroup of k_runs_x
+    const unsigned row_blocks = (unsigned)((r * r + run_rows - 1) / run_rows), line_blocks = (unsigned)((r + rows - 1) / rows);
     const bool words = r % 4 == 0 && reinterpret_cast<uintptr_t>(out) % 4 == 0;
     for (int o = 0; o < (sc.single ? 8 : 1); ++o) {
         const int sx = o & 1, sy = o >> 1 & 1, sz = o >> 2;
@@ -527,25 +532,18 @@ hipError_t octant_extents(const OccLevels &lv, uint8_t *scratch, uint8_t *out, h
         if (sc.single) {
             sc.gx[0] = sc.gx[1] = nullptr;
             sc.gx[sx] = next();
-            sc.gy[sy] = next();
-            sc.gz[sz] = next();
             sc.fxy[sx | sy << 1] = next();
             sc.fxz[sx | sz << 1] = next();
         } else {
-            for (int i = 0; i < 2; ++i) {
-                sc.gx[i] = next();
-                sc.gy[i] = next();
-                sc.gz[i] = next();
-            }
+            for (int i = 0; i < 2; ++i) sc.gx[i] = next();
             for (int i = 0; i < 4; ++i) {
                 sc.fxy[i] = next();
                 sc.fxz[i] = next();
             }
         }
         const unsigned combos = sc.single ? 1 : 4, octants = sc.single ? 1 : 8;
-        hipLaunchKernelGGL(k_runs_x<N>, dim3(row_blocks), dim3(64), 0, stream, lv, sc);
-        hipLaunchKernelGGL((k_squares_x<N, false>), dim3(line_blocks, combos), dim3(64), 0, stream, sc, sx | sy << 1);
-        hipLaunchKernelGGL((k_squares_x<N, true>), dim3(line_blocks, combos), dim3(64), 0, stream, sc, sx | sz << 1);
+        hipLaunchKernelGGL(k_runs_x<16>, dim3(row_blocks), dim3(64 * kRunWaves), 0, stream, lv, sc);
+        hipLaunchKernelGGL(k_squares_x<N>, dim3(line_blocks, combos, 2), dim3(64), 0, stream, sc, sx | sy << 1, sx | sz << 1);
         hipLaunchKernelGGL(k_extents<N>, dim3(line_blocks, octants), dim3(64), 0, stream, sc, o, words,
                            out + (sc.single ? (size_t)o * n : 0));
     }
@@ -554,8 +552,8 @@ hipError_t octant_extents(const OccLevels &lv, uint8_t *scratch, uint8_t *out, h
 
 }  // namespace
 
-// A row of up to 256 cells takes at most 64 lanes of four; larger ones have 16
-// cells a lane.
+// The marching steps: a row of up to 256 cells takes at most 64 lanes of four
+// (few lines march, so each takes more lanes); larger ones have 16 cells a lane.
 hipError_t launch_octant_extents(const OccLevels &lv, uint8_t *scratch, uint8_t *out, hipStream_t stream) {
     const int r = lv.res[lv.n - 1];
     if (r <= 0 || r > kMaxDistRes) return hipErrorInvalidValue;
