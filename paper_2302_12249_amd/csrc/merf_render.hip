@@ -1175,16 +1175,19 @@ struct MeasureArgs {
 
 // One wave renders local tile lt of camera cam (launch tile `tile`, used by
 // the measurement outputs only) of scene sc; lane = threadIdx.x.
-template <int kMode, int kMlpPrec, int kFeat, bool kLevels, typename S, typename Cam>
+// kPart: only the pixels of `part`, the tile's lanes of which lane >> part_shift
+// is `part`; the others idle as those outside the image do.
+template <int kMode, int kMlpPrec, int kFeat, bool kLevels, bool kPart = false, typename S, typename Cam>
 __device__ __forceinline__ void render_tile(const S &sc, const Cam &cam, int lt, int tile,
-                                            const TileParams tp, const MeasureArgs ma, float *lds, const int lane) {
+                                            const TileParams tp, const MeasureArgs ma, float *lds, const int lane,
+                                            int part = 0, int part_shift = 6) {
     constexpr bool kStats = kMode >= 1, kPhase = kMode == 2;
     // the tile's corner is uniform: kept in scalar registers
     const int tx0 = __builtin_amdgcn_readfirstlane((lt % cam.tiles_x) * kTile);
     const int ty0 = __builtin_amdgcn_readfirstlane((lt / cam.tiles_x) * kTile);
     const int px = tx0 + (lane & (kTile - 1));
     const int py = ty0 + (lane / kTile);
-    const bool active = px < cam.width && py < cam.height;
+    const bool active = px < cam.width && py < cam.height && (!kPart || lane >> part_shift == part);
     PhaseClock<kPhase> ph;
     ph.start();
 
@@ -1524,6 +1527,29 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
     const MeasureArgs ma = {rb.stats, rb.rec, rb.rec_count, rb.rec_cap, rb.total_tiles, rb.phases};
     render_tile<kMode, kMlpPrec, kFeat, kLevels>(sc, cam, tile - cam.tile_start, tile, tp, ma, lds,
                                                     (int)threadIdx.x);
+}
+
+// A launch of so few tiles that their waves leave slots of the device idle: each
+// tile is rendered by 1 << parts_log2 waves, a part of its pixels each.  A small
+// frame lasts as long as its longest wave, and a wave's rounds follow its
+// rays' samples: with 16 rays instead of 64 there are fewer of them
+// (parking_depth), and its march waits for fewer rays.  Full scene, back to
+// back: 128x128 52.6 -> 37.8 us, 200x150 58.6 -> 49; 8x8 pixels 29.7 -> 23.6.
+template <int kMlpPrec, int kFeat, bool kLevels>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_render_parts(const DevScene sc, const RenderBatch rb,
+                                                                                              const int parts_log2) {
+    __shared__ float lds[kLdsFloats<kMlpPrec>];
+    const int slot = xcd_remap((int)blockIdx.x, rb.total_tiles << parts_log2);
+    const int tile = slot >> parts_log2, part = slot & ((1 << parts_log2) - 1);
+    int c = 0;
+#pragma unroll
+    for (int i = 1; i < kCamsPerLaunch; ++i)
+        if (i < rb.n_cams && tile >= rb.cams[i].tile_start) c = i;
+    const DevCamera &cam = rb.cams[c];
+    const TileParams tp = {rb.step, rb.inv_step, rb.t_min, rb.delta_mode};
+    const MeasureArgs ma = {};
+    render_tile<0, kMlpPrec, kFeat, kLevels, true>(sc, cam, tile - cam.tile_start, tile, tp, ma, lds,
+                                                      (int)threadIdx.x, part, 6 - parts_log2);
 }
 
 // Served launch: workgroup b renders position b / 8 of its XCD's share of
@@ -1897,6 +1923,32 @@ const void *render_kernel(const RenderBatch &rb) {
 dim3 render_grid(const RenderBatch &rb) { return dim3((unsigned)rb.total_tiles); }
 
 template <int kFeat, bool kLevels>
+const void *parts_kernel_mlp(int mlp_prec) {
+    return mlp_prec == 0 ? (const void *)k_render_parts<0, kFeat, kLevels>
+         : mlp_prec == 1 ? (const void *)k_render_parts<1, kFeat, kLevels>
+                         : (const void *)k_render_parts<2, kFeat, kLevels>;
+}
+
+template <bool kLevels>
+const void *parts_kernel(const RenderBatch &rb) {
+    return rb.feat_prec == 2 ? parts_kernel_mlp<2, kLevels>(rb.mlp_prec)
+         : rb.feat_prec == 1 ? parts_kernel_mlp<1, kLevels>(rb.mlp_prec)
+                             : parts_kernel_mlp<0, kLevels>(rb.mlp_prec);
+}
+
+// Waves a tile of a launch is divided over (log2): up to eight, as long as they
+// take at most half of the device's slots.  With all 4096, 256x256 gains one
+// more percent alone, but loses 11% where four streams render such frames side
+// by side (17.8 -> 19.8 us each; 16.5 with half of them); with more, waves queue
+// (256x256 59 -> 63 us).  Sixteen waves a tile gain only below 64 tiles.
+int render_parts_log2(const RenderBatch &rb) {
+    int k = 0;
+    if (rb.stats || rb.phases || rb.order) return k;
+    while (k < kPartsMaxLog2 && (int64_t)rb.total_tiles << (k + 1) <= kPartsMaxWaves) ++k;
+    return k;
+}
+
+template <int kFeat, bool kLevels>
 const void *served_kernel_mlp(int mlp_prec) {
     return mlp_prec == 0 ? (const void *)k_render_served<0, kFeat, kLevels>
          : mlp_prec == 1 ? (const void *)k_render_served<1, kFeat, kLevels>
@@ -1926,6 +1978,11 @@ hipError_t launch_render_served(const DevScene *table, const ServeLaunch *launch
 
 hipError_t launch_render(const DevScene &sc, const RenderBatch &rb, hipStream_t stream) {
     if (rb.total_tiles <= 0) return hipSuccess;
+    if (int parts_log2 = render_parts_log2(rb)) {
+        void *args[] = {const_cast<DevScene *>(&sc), const_cast<RenderBatch *>(&rb), &parts_log2};
+        return hipLaunchKernel(rb.skip_mode ? parts_kernel<true>(rb) : parts_kernel<false>(rb),
+                               dim3((unsigned)rb.total_tiles << parts_log2), dim3(kRenderBlock), args, 0, stream);
+    }
     void *args[] = {const_cast<DevScene *>(&sc), const_cast<RenderBatch *>(&rb)};
     return hipLaunchKernel(render_kernel(rb), render_grid(rb), dim3(kRenderBlock), args, 0, stream);
 }
