@@ -34,7 +34,7 @@ constexpr int kCostRays = 4;
 constexpr int kCostKeys = kCostRays + 1;         // keys 0 .. 4: classes of estimated effort (k_tile_cost)
 constexpr int kOrderMinTiles = 6144;
 // Launches whose tiles are divided over several waves each (k_render_parts).
-constexpr int kPartsMaxLog2 = 3, kPartsMaxWaves = 2048;
+constexpr int kPartsMaxLog2 = 3, kPartsMaxWaves = 3072;
 constexpr int kOrderMaxTiles = 1 << 17;
 
 // Scene as laid out in device memory.

@@ -1937,10 +1937,12 @@ const void *parts_kernel(const RenderBatch &rb) {
 }
 
 // Waves a tile of a launch is divided over (log2): up to eight, as long as they
-// take at most half of the device's slots.  With all 4096, 256x256 gains one
-// more percent alone, but loses 11% where four streams render such frames side
-// by side (17.8 -> 19.8 us each; 16.5 with half of them); with more, waves queue
-// (256x256 59 -> 63 us).  Sixteen waves a tile gain only below 64 tiles.
+// take at most three quarters of the device's 4096 slots.  With all of them, frames of
+// 256x256 or 352x368 pixels gain a little more alone but lose 11% where four
+// streams render them side by side (17.8 -> 19.8 and 20.3 -> 22.6 us each); with
+// half of them, 304x320 gains nothing (68.7 us alone and 20.3 on four streams,
+// against 58.5 and 19.1).  Beyond 4096, waves queue (256x256 52 -> 63 us).
+// Sixteen waves a tile gain only below 64 tiles.
 int render_parts_log2(const RenderBatch &rb) {
     int k = 0;
     if (rb.stats || rb.phases || rb.order) return k;

@@ -42,8 +42,9 @@ def both(torch, merf, renderer, cams, **params):
     return a.cpu().numpy(), b.cpu().numpy()
 
 
-# tiles 1, 2, 256 | 257, 512 | 513, 1024 | 1025
-@pytest.mark.parametrize("w,h", [(1, 1), (9, 7), (128, 128), (2056, 8), (125, 255), (4104, 8), (255, 249), (1639, 35)])
+# tiles 1, 2, 256, 257, 384 | 385, 512, 513, 768 | 769, 1024, 1025, 1536 | 1537
+@pytest.mark.parametrize("w,h", [(1, 1), (9, 7), (128, 128), (2056, 8), (3072, 8), (3080, 8), (125, 255), (4104, 8),
+                                 (255, 190), (6152, 8), (255, 249), (1639, 35), (383, 255), (231, 423)])
 def test_divided_tiles_give_the_same_image(torch, merf, renderer, w, h):
     a, b = both(torch, merf, renderer, synth.orbit_cameras(1, w=w, h=h))
     assert np.array_equal(a, b)
