@@ -311,7 +311,12 @@ struct SampleResult {
 // One evaluated sample: gather, dequantise, decode.
 // All offsets are 32-bit (the upload keeps every array below 2 GiB) and are
 // added to uniform base pointers, so no 64-bit address arithmetic runs per lane.
-template <int kFeat, typename S>
+// kFolded: the sigmoid's -log2(e) lies in the scale of the codes, an operation
+// less per channel.  That moves the sums by their last bits, which a float32
+// MLP passes on as they are; one with float16 or bfloat16 operands rounds some
+// of them to its next value (up to 9e-4 of a pixel), so those modes multiply
+// separately, with the roundings of a plain sigmoid(m (2b/255 - 1)).
+template <int kFeat, bool kFolded, typename S>
 __device__ __forceinline__ SampleResult eval_sample(const S &sc, float3 p, float delta) {
     const Footprint f = footprint(sc, p);
     const Texels x = gather(sc, f);
@@ -398,6 +403,11 @@ __device__ __forceinline__ SampleResult eval_sample(const S &sc, float3 p, float
         float sa[7];
 #pragma unroll
         for (int c = 0; c < 7; ++c) sa[c] = 0.0f;
+        // Eq. 8 of the interpolated codes, times -log2(e) for the sigmoid
+        auto exponent = [&](float codes) {
+            if constexpr (kFolded) return fmaf(codes, sc.f_scale24_l2, sc.f_off_l2);
+            else return fmaf(codes, sc.f_scale24, sc.f_off) * kNegLog2e;
+        };
         if constexpr (kFeat == 2) {
             // texel pairs (2k, 2k + 1): their weights and the codes of one
             // channel in one register each
@@ -414,7 +424,7 @@ __device__ __forceinline__ SampleResult eval_sample(const S &sc, float3 p, float
                 sa[6] = __builtin_amdgcn_fdot2(wk, codes_jj<3>(ha, hb), sa[6], false);
             }
 #pragma unroll
-            for (int c = 0; c < 7; ++c) sa[c] = fmaf(sa[c], sc.f_scale24_l2, sc.f_off_l2);
+            for (int c = 0; c < 7; ++c) sa[c] = exponent(sa[c]);
         } else if constexpr (kFeat == 1) {
             const float af = sc.f_scale24;
 #pragma unroll
@@ -452,7 +462,7 @@ __device__ __forceinline__ SampleResult eval_sample(const S &sc, float3 p, float
                 }
             }
 #pragma unroll
-            for (int c = 0; c < 7; ++c) sa[c] = fmaf(sa[c], sc.f_scale24_l2, sc.f_off_l2);
+            for (int c = 0; c < 7; ++c) sa[c] = exponent(sa[c]);
         }
 #pragma unroll
         for (int c = 0; c < 7; ++c) r.sg[c] = sigmoid_l2(sa[c]);
@@ -1261,7 +1271,7 @@ __device__ __forceinline__ void render_tile(const S &sc, const Cam &cam, int lt,
         if (lane < total) {
             const int e = imap[lane];
             const float4 q = pq[e];
-            const SampleResult r = eval_sample<kFeat>(sc, make_float3(q.x, q.y, q.z), q.w);
+            const SampleResult r = eval_sample<kFeat, kMlpPrec == 0>(sc, make_float3(q.x, q.y, q.z), q.w);
             rs[2 * lane] = make_float4(r.trans, r.sg[0], r.sg[1], r.sg[2]);
             rs[2 * lane + 1] = make_float4(r.sg[3], r.sg[4], r.sg[5], r.sg[6]);
         }
@@ -1558,7 +1568,7 @@ __global__ __launch_bounds__(64) void k_tile_cost(const DevScene sc, const Rende
                     ev = 1;
                     break;
                 }
-                T *= eval_sample<0>(sc, p, u1 - u0).trans;
+                T *= eval_sample<0, true>(sc, p, u1 - u0).trans;
                 if (++ev >= kCostEval || T < rb.t_min) break;
                 s.k += 1.0f;
             } else {
