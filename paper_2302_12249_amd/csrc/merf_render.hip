@@ -648,32 +648,44 @@ struct MlpLds {
     static constexpr int kFloats = 64 * (kPrec == 0 ? 37 : 26);
 };
 
-// Sine and cosine for |x| <= 1 by their Taylor series to x^9 and x^10 (errors
-// below 6e-8): as many issue slots as the hardware's, which are exact to 1e-6
-// only, and the doublings below multiply that by 8.
-__device__ __forceinline__ void sincos_unit(float x, float &s, float &c) {
+// Scale of the split fp32 MLP's inputs, which are at most 1 (deferred_mlp_split).
+constexpr int kInputScaleLog2 = 15;
+
+// Sine and cosine for |x| <= 1, times kScale (a power of two), by their Taylor
+// series to x^9 and x^10 (errors below 6e-8): as many issue slots as the
+// hardware's, which are exact to 1e-6 only, and the doublings below multiply
+// that by 8.  kx is kScale x.
+template <int kScale>
+__device__ __forceinline__ void sincos_unit(float x, float kx, float &s, float &c) {
+    constexpr float K = (float)kScale;
     const float x2 = x * x;
-    s = fmaf(x * x2, fmaf(fmaf(fmaf(2.7557319e-6f, x2, -1.9841270e-4f), x2, 8.3333333e-3f), x2, -0.16666667f), x);
-    c = fmaf(fmaf(fmaf(fmaf(fmaf(-2.7557319e-7f, x2, 2.4801587e-5f), x2, -1.3888889e-3f), x2, 4.1666667e-2f), x2, -0.5f),
-             x2, 1.0f);
+    s = fmaf(kx * x2, fmaf(fmaf(fmaf(2.7557319e-6f, x2, -1.9841270e-4f), x2, 8.3333333e-3f), x2, -0.16666667f), kx);
+    c = fmaf(fmaf(fmaf(fmaf(fmaf(K * -2.7557319e-7f, x2, K * 2.4801587e-5f), x2, K * -1.3888889e-3f), x2, K * 4.1666667e-2f),
+                  x2, K * -0.5f),
+             x2, K);
 }
 
-template <bool kSeries>
+// The MLP's 34 inputs, times kScale (1, or a power of two), zero-padded to 48.
+template <bool kSeries, int kScale = 1>
 __device__ __forceinline__ void mlp_encode(float *x, const Accum &acc, float3 d) {
-    x[0] = acc.cd0; x[1] = acc.cd1; x[2] = acc.cd2;
-    x[3] = acc.f0; x[4] = acc.f1; x[5] = acc.f2; x[6] = acc.f3;
-    x[7] = d.x; x[8] = d.y; x[9] = d.z;
+    constexpr float K = (float)kScale;
+    x[0] = K * acc.cd0; x[1] = K * acc.cd1; x[2] = K * acc.cd2;
+    x[3] = K * acc.f0; x[4] = K * acc.f1; x[5] = K * acc.f2; x[6] = K * acc.f3;
+    x[7] = K * d.x; x[8] = K * d.y; x[9] = K * d.z;
     // sin and cos of 2^k d, k = 0..3: sine and cosine at k = 0 (the series, or
     // the hardware's in the reduced-precision modes), then the double-angle
     // identities sin 2a = 2 sin a cos a and
     // cos 2a = 1 - 2 sin^2 a (three FP32 operations instead of two quarter-
-    // rate transcendentals per term; the error stays near 1e-5 absolute)
+    // rate transcendentals per term; the error stays near 1e-5 absolute).
+    // A scale rides along at no cost: every step is the same operation on
+    // scaled values, with the same rounding.
     float sn[3], cs[3];
     if constexpr (kSeries) {
-        sincos_unit(d.x, sn[0], cs[0]);
-        sincos_unit(d.y, sn[1], cs[1]);
-        sincos_unit(d.z, sn[2], cs[2]);
+        sincos_unit<kScale>(d.x, x[7], sn[0], cs[0]);
+        sincos_unit<kScale>(d.y, x[8], sn[1], cs[1]);
+        sincos_unit<kScale>(d.z, x[9], sn[2], cs[2]);
     } else {
+        static_assert(kSeries || kScale == 1, "the hardware's sines are not scaled");
         sn[0] = __sinf(d.x); sn[1] = __sinf(d.y); sn[2] = __sinf(d.z);
         cs[0] = __cosf(d.x); cs[1] = __cosf(d.y); cs[2] = __cosf(d.z);
     }
@@ -683,8 +695,8 @@ __device__ __forceinline__ void mlp_encode(float *x, const Accum &acc, float3 d)
         for (int a = 0; a < 3; ++a) {
             x[10 + 3 * k + a] = sn[a];
             x[22 + 3 * k + a] = cs[a];
-            const float s2 = 2.0f * sn[a];
-            cs[a] = fmaf(-s2, sn[a], 1.0f);
+            const float s2 = (2.0f / K) * sn[a];
+            cs[a] = fmaf(-s2, sn[a], K);
             sn[a] = s2 * x[22 + 3 * k + a];
         }
     }
@@ -716,20 +728,30 @@ __device__ __forceinline__ floatx4 mfma16(half4_t<kPrec> a, half4_t<kPrec> b, fl
 // costs its 32 cycles in full (12 fewer of the 68 made a 1080p frame 2.1%
 // faster): the vector units wait for it, as they do not for a float16 one.  So
 // every operand v is split into two float16 values, h = RN16(v) and
-// l = RN16(v - h), which hold it to 2^-23 relative, and a product becomes all
-// four of (h + l)(h' + l') in float32 accumulation.  A K = 32 instruction
-// takes h and l of 16 inputs as its 32 slots (a lane's eight: h, then l, of
-// the four inputs that the layout gives it), once against the weights' h and
-// once against their l: 36 instructions of 16 cycles and no conversions of
-// weights, which the upload splits and lays out by lane (k_mlp_fragments).
-// Weights and hidden units are scaled by powers of two (undone exactly in the
-// multiply that adds the bias), so that neither overflows float16 nor loses
-// its l to underflow, whatever their magnitudes; a scene whose parameters are
-// not finite, or beyond that scaling, takes the float32 instructions instead.
-// Against float64 (an empty scene, where the image is h alone) the error falls
-// from 1.04e-7 to 0.67e-7 of the values' norm: the split adds 3% to it, the
-// series of mlp_encode takes away 40%.  1080p 269 -> 258 us, sixteen 1080p
-// views 3.27 -> 3.07 ms, 512x512 85.6 -> 84.0 us.
+// l = RN16(v - h), and a product becomes all four of (h + l)(h' + l') in float32
+// accumulation.  A K = 32 instruction takes h and l of 16 inputs as its 32 slots
+// (a lane's eight: h, then l, of the four inputs that the layout gives it), once
+// against the weights' h and once against their l: 36 instructions of 16 cycles
+// and no conversions of weights, which the upload splits and lays out by lane
+// (k_mlp_fragments).
+// h + l is v to 2^-23 relative, until l reaches float16's smallest step of
+// 2^-24: below that it is v to an absolute 2^-25.  So every operand is scaled by
+// a power of two to the top of float16's range (undone exactly in the multiply
+// that adds the bias): the inputs, which are at most 1, by 2^15, a layer's
+// weights by the largest of them and its hidden units by their bound, to 2^14
+// .. 2^15.  The absolute error is then 2^-39 of what the scale is taken from (an
+// input of 1, the layer's largest weight, the bound of its hidden units), and
+// an operand down to 2^-16 of that keeps the full 2^-23.  A scene whose
+// parameters are not finite, or beyond that scaling, takes the float32
+// instructions instead.
+// Error against float64 (2-norm, six MLPs of normal weights, colours and
+// features near 1e-3, 0.1 and 1): 3.4e-7, 3.4e-7 and 3.5e-7 of the values, where
+// the float32 instructions with the hardware's sines had 5.9e-7, 6.0e-7 and
+// 5.8e-7: mlp_encode's series takes away more than the split adds.  With all of
+// the direction's weights zero the split shows alone: 1.7e-7 in each against
+// 1.1e-7, 1.1e-7 and 1.3e-7 (unscaled inputs: 4.1e-5, 3.2e-7 and 2.0e-7).
+// 1080p 269 -> 258 us, sixteen 1080p views 3.27 -> 3.07 ms, 512x512 85.6 -> 84.0
+// us; the scale of the inputs changes none of them.
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_f16(float a, float b) {
@@ -783,7 +805,7 @@ __device__ __forceinline__ float3 deferred_mlp_split(const float *__restrict__ W
     uint8_t *rows = reinterpret_cast<uint8_t *>(xs);
     {
         float x[48];
-        mlp_encode<true>(x, acc, d);
+        mlp_encode<true, (1 << kInputScaleLog2)>(x, acc, d);
         uint8_t *row = rows + lane * kSplitRow;
 #pragma unroll
         for (int q = 0; q < 8; ++q) *reinterpret_cast<u32x4 *>(row + 16 * q) = split4(x + 4 * q, minus_one);
@@ -791,22 +813,27 @@ __device__ __forceinline__ float3 deferred_mlp_split(const float *__restrict__ W
         *reinterpret_cast<uint2 *>(row + 128) = make_uint2(t.x, t.z);
     }
     __syncthreads();
+    // the weights' low parts first: the sums then round once at their full
+    // size for each of the high parts only
     floatx4 c[4];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-        const uint8_t *row = rows + (16 * mt + j) * kSplitRow;
-        const uint2 t = *reinterpret_cast<const uint2 *>(row + 128);
-        const u32x4 tail = {t.x, t.y, 0u, 0u};
-        c[mt] = mfma32(w1[4], tail, floatx4{0.0f, 0.0f, 0.0f, 0.0f});
+    for (int mt = 0; mt < 4; ++mt) c[mt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int low = 1; low >= 0; --low) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) {
+                const u32x4 b = *reinterpret_cast<const u32x4 *>(rows + (16 * mt + j) * kSplitRow + 16 * (4 * m + g));
+                c[mt] = mfma32(w1[2 * m + low], b, c[mt]);
+            }
+        if (low)
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) {
+                const uint2 t = *reinterpret_cast<const uint2 *>(rows + (16 * mt + j) * kSplitRow + 128);
+                c[mt] = mfma32(w1[4], u32x4{t.x, t.y, 0u, 0u}, c[mt]);
+            }
     }
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            const u32x4 b = *reinterpret_cast<const u32x4 *>(rows + (16 * mt + j) * kSplitRow + 16 * (4 * m + g));
-            c[mt] = mfma32(w1[2 * m], b, c[mt]);
-            c[mt] = mfma32(w1[2 * m + 1], b, c[mt]);
-        }
 #pragma unroll
     for (int layer = 0; layer < 2; ++layer) {
         const u32x4 wh = F[64 * (layer ? kFragL3 : kFragL2)], wl = F[64 * ((layer ? kFragL3 : kFragL2) + 1)];
@@ -821,9 +848,9 @@ __device__ __forceinline__ float3 deferred_mlp_split(const float *__restrict__ W
             b[mt] = split4(h, minus_one);
         }
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) c[mt] = mfma32(wh, b[mt], floatx4{0.0f, 0.0f, 0.0f, 0.0f});
+        for (int mt = 0; mt < 4; ++mt) c[mt] = mfma32(wl, b[mt], floatx4{0.0f, 0.0f, 0.0f, 0.0f});
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) c[mt] = mfma32(wl, b[mt], c[mt]);
+        for (int mt = 0; mt < 4; ++mt) c[mt] = mfma32(wh, b[mt], c[mt]);
     }
     __syncthreads();   // every lane has read its inputs; reuse xs for the outputs
     const float *b2 = W + kMlpParams - kMlpOut;
@@ -868,16 +895,17 @@ __global__ __launch_bounds__(64) void k_mlp_fragments(const float *__restrict__ 
         bound2 += fabsf(b1[lane]);
     }
     bound2 = reduce_max(bound2);
-    // exponents: weights up to 2^10 and hidden units up to 2^13 as float16
+    // exponents: the largest weight and the bound of the hidden units to
+    // 2^14 .. 2^15 as float16
     auto exponent = [](float largest, int want) { return largest > 0.0f && largest < kInf ? want - ilogbf(largest) : 0; };
-    const int a0 = exponent(largest(W0, kMlpIn * kMlpHidden), 9), a1 = exponent(largest(W1, kMlpHidden * kMlpHidden), 9),
-              a2 = exponent(largest(W2, kMlpHidden * kMlpOut), 9), q1 = exponent(bound1, 12), q2 = exponent(bound2, 12);
+    const int a0 = exponent(largest(W0, kMlpIn * kMlpHidden), 14), a1 = exponent(largest(W1, kMlpHidden * kMlpHidden), 14),
+              a2 = exponent(largest(W2, kMlpHidden * kMlpOut), 14), q1 = exponent(bound1, 14), q2 = exponent(bound2, 14);
     const bool ok = __builtin_amdgcn_ballot_w64(!finite) == 0 && bound1 < kInf && bound2 < kInf &&
                     max(max(abs(a0), abs(a1)), max(max(abs(a2), abs(q1)), abs(q2))) <= 40;
     if (lane == 0) {
         float *head = reinterpret_cast<float *>(out);
         out[0] = ok ? 1u : 0u;
-        head[1] = ldexpf(1.0f, ok ? q1 - a0 : 0);
+        head[1] = ldexpf(1.0f, ok ? q1 - a0 - kInputScaleLog2 : 0);
         head[2] = ldexpf(1.0f, ok ? q2 - a1 - q1 : 0);
         head[3] = ldexpf(1.0f, ok ? -a2 - q2 : 0);
     }
