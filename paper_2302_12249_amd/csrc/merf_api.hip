@@ -484,32 +484,30 @@ void trim_scratch() {
 }
 
 // Scratch of n bytes, ordered on stream; from the pool up to its size, else
-// (and on a stream that is capturing) allocated and freed plainly.  So are
-// small ones, which hipMalloc and hipFree serve 18 us faster than the pool
-// (an octant grid of 26^3 cells 37 us instead of 56; from 1 MiB it turns).
+// (and on a stream that is capturing) allocated and freed by dev_alloc and
+// dev_free, so that a stream-ordered upload's waits for nothing else on the
+// device either.  So are small ones, which hipMalloc and hipFree serve 18 us
+// faster than the pool (an octant grid of 26^3 cells 37 us instead of 56; from
+// 1 MiB it turns).
 struct Scratch {
     void *p = nullptr;
-    bool pooled = false;
-    hipError_t alloc(size_t n, hipStream_t stream) {
+    bool by_stream = false;             // freed in stream order
+    hipError_t alloc(size_t n, bool ordered, hipStream_t stream) {
         hipMemPool_t pool = n >= kScratchPooled && n <= kScratchKept && !capturing(stream) ? scratch_pool() : nullptr;
-        if (pool && hipMallocFromPoolAsync(&p, n, pool, stream) == hipSuccess && p) {
-            pooled = true;
-            return hipSuccess;
-        }
+        by_stream = true;
+        if (pool && hipMallocFromPoolAsync(&p, n, pool, stream) == hipSuccess && p) return hipSuccess;
         if (pool) (void)hipGetLastError();
-        return plain(n);
-    }
-    hipError_t plain(size_t n) {
-        hipError_t e = hipMalloc(&p, n);
+        by_stream = ordered;
+        hipError_t e = dev_alloc(&p, n, ordered, stream);
         if (e != hipSuccess) {
             (void)hipGetLastError();
             trim_scratch();
-            e = hipMalloc(&p, n);
+            e = dev_alloc(&p, n, ordered, stream);
         }
         return e;
     }
     void free(hipStream_t stream) {
-        if (p) (void)(pooled ? hipFreeAsync(p, stream) : hipFree(p));
+        if (p) (void)dev_free(p, by_stream, stream);
         p = nullptr;
     }
 };
@@ -718,9 +716,9 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
         trim_scratch();
         e = dev_alloc(&base, total, ordered, stream);
     }
-    if (e == hipSuccess) e = scratch.alloc(staging, stream);
+    if (e == hipSuccess) e = scratch.alloc(staging, ordered, stream);
     // allocation failures surface here; and the copies use streams of their own
-    if (e == hipSuccess && (ordered || scratch.pooled)) e = hipStreamSynchronize(stream);
+    if (e == hipSuccess && scratch.by_stream) e = hipStreamSynchronize(stream);
     void *stage = scratch.p;
     if (e != hipSuccess || !base || !stage) {
         (void)hipGetLastError();
@@ -1158,7 +1156,7 @@ int merf_distance_grid(const uint8_t *const *occ_dev, const int32_t *res, int32_
     const size_t r = (size_t)res[n_levels - 1], n = r * r * r;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     Scratch tmp;
-    hipError_t e = tmp.alloc(2 * align_up(n, 256), stream);
+    hipError_t e = tmp.alloc(2 * align_up(n, 256), false, stream);
     if (e != hipSuccess || !tmp.p) {
         (void)hipGetLastError();
         return fail(MERF_E_OOM, "hipMalloc of %zu scratch bytes failed", 2 * align_up(n, 256));
@@ -1180,7 +1178,7 @@ int merf_octant_extent_grid(const uint8_t *const *occ_dev, const int32_t *res, i
     const size_t bytes = octant_scratch_bytes(res[n_levels - 1]);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     Scratch tmp;
-    hipError_t e = tmp.alloc(bytes, stream);
+    hipError_t e = tmp.alloc(bytes, false, stream);
     if (e != hipSuccess || !tmp.p) {
         (void)hipGetLastError();
         return fail(MERF_E_OOM, "hipMalloc of %zu scratch bytes failed", bytes);

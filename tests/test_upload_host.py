@@ -1,0 +1,79 @@
+"""The host side of uploads on the CPU: csrc/merf_api.hip over a stand-in for
+the HIP runtime (fake_hip.cpp), which counts what waits for the device and has
+as much memory as a test gives it."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import synth
+from paper_2302_12249_amd import merf
+from scene_builders import dense_scene
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2302_12249_amd", "csrc")
+INCLUDE = os.path.join(os.path.dirname(HERE), "include")
+
+
+def build(out):
+    flags = ["-std=c++17", "-O1", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__", "-D__align__(n)=__attribute__((aligned(n)))",
+             "-DHIP_SYMBOL(x)=&x", "-I/opt/rocm/include", "-I" + INCLUDE, "-I" + CSRC]
+    subprocess.run(["g++", *flags, "-shared", "-Wl,-Bsymbolic", "-x", "c++", os.path.join(CSRC, "merf_api.hip"),
+                    os.path.join(HERE, "fake_hip.cpp"), "-o", out, "-pthread"], check=True)
+
+
+@pytest.fixture(scope="module")
+def so(tmp_path_factory):
+    path = str(tmp_path_factory.mktemp("fake") / "libmerf_fake.so")
+    build(path)
+    return path
+
+
+@pytest.fixture()
+def lib(so, tmp_path):
+    """A library of its own for each test: the state of uploads is the process's."""
+    path = str(tmp_path / "libmerf_fake.so")
+    with open(so, "rb") as f, open(path, "wb") as g:
+        g.write(f.read())
+    lib = C.CDLL(path)
+    for name in ("fake_held", "fake_pool_kept", "fake_pinned", "fake_peak", "merf_hbm_in_use"):
+        getattr(lib, name).restype = C.c_size_t
+    lib.fake_capacity.argtypes = [C.c_size_t]
+    lib.merf_set_hbm_budget.argtypes = [C.c_size_t]
+    lib.fake_waits.restype = C.c_long
+    lib.merf_free.argtypes = lib.fake_release_on.argtypes = [C.c_void_p]
+    lib.merf_last_error.restype = C.c_char_p
+    return lib
+
+
+def upload(lib, scene, ordered=False):
+    d, keep = merf.scene_desc(scene)
+    h = C.c_void_p()
+    rc = (lib.fake_upload_on if ordered else lib.merf_scene_upload)(C.byref(d), C.byref(h))
+    del keep
+    return rc, h.value
+
+
+def large_scene():
+    """300 MB of blocks and the rest small: its scratch is beyond what is kept."""
+    sc = dense_scene(L=16, R=16)
+    nb = 42
+    sc.L, sc.block_index = 8 * nb, np.arange(nb ** 3, dtype=np.int32)
+    sc.blocks = np.zeros((nb ** 3, 8, 8, 8, 8), np.uint8)
+    return sc
+
+
+SCENES = {"small": lambda: dense_scene(L=16, R=16), "medium": lambda: dense_scene(L=64, R=1024), "large": large_scene}
+
+
+@pytest.mark.parametrize("size", sorted(SCENES))
+def test_ordered_uploads_wait_for_no_other_work(lib, size):
+    """The serving runtime's uploads: no call in them waits for the device."""
+    sc = SCENES[size]()
+    before = lib.fake_waits()
+    rc, h = upload(lib, sc, ordered=True)
+    assert rc == 0 and lib.fake_waits() == before
+    assert lib.fake_release_on(h) == 0 and lib.fake_waits() == before
+    assert lib.merf_hbm_in_use() == 0 and lib.fake_held() == lib.fake_pool_kept()
