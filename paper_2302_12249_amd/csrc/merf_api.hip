@@ -652,7 +652,8 @@ hipError_t upload_copies(const std::vector<Copy> &copies, bool ordered, hipStrea
     return staged.empty() ? hipSuccess : ring.run(staged);
 }
 
-// After the last scene is freed: what was not used lately goes back.
+// What was not used lately goes back (hipHostFree and hipStreamDestroy wait for
+// the device).
 void release_idle() {
     const Clock::time_point now = Clock::now();
     bool idle;
@@ -926,9 +927,12 @@ int scene_release_on(merf_scene_t s, hipStream_t stream) {
     const hipError_t e = dev_free(s->dev_base, s->ordered, stream);
     s->magic = 0;
     delete s;
-    if (no_scene_left()) release_idle();
     if (e != hipSuccess) return hip_fail(e, "scene release");
     return MERF_OK;
+}
+
+void release_unused() {
+    if (no_scene_left()) release_idle();
 }
 
 }  // namespace merf
@@ -945,7 +949,7 @@ int merf_free(merf_scene_t s) {
     if (e2 == hipSuccess && s->ordered) e2 = hipStreamSynchronize(nullptr);
     s->magic = 0;
     delete s;
-    if (no_scene_left()) release_idle();
+    release_unused();
     if (e1 != hipSuccess) return hip_fail(e1, "hipDeviceSynchronize (merf_free)");
     if (e2 != hipSuccess) return hip_fail(e2, "hipFree (merf_free)");
     return MERF_OK;

@@ -29,6 +29,10 @@ int scene_upload_on(const merf_scene_desc *desc, hipStream_t stream, merf_scene_
 // for other work on the device: the caller guarantees that no queued or
 // running work reads it.
 int scene_release_on(merf_scene_t s, hipStream_t stream);
+// Give back the scratch and pinned buffers that uploads keep for the next, if
+// no scene is left and they were not used lately.  May wait for the device, so
+// scene_release_on does not.
+void release_unused();
 
 // A scene's device image: the bytes of its device allocation once an upload
 // has built it (packed bricks, occupancy levels, empty-space grids, planes,

@@ -709,6 +709,7 @@ int merf_server_destroy(merf_server_t S) {
     if (hipStreamSynchronize(S->load_stream) != hipSuccess) rc = MERF_E_DEVICE;
     destroy_slots(S);
     delete S;
+    release_unused();
     return rc;
 }
 

@@ -155,6 +155,7 @@ size_t fake_pinned() {
 size_t fake_peak(int reset) { const size_t v = peak; if (reset) peak = plain + pool_reserved(); return v; }
 long fake_waits() { return waits; }
 int fake_upload_on(const merf_scene_desc *d, merf_scene_t *out) { return merf::scene_upload_on(d, reinterpret_cast<hipStream_t>(8), out); }
+void fake_release_unused() { merf::release_unused(); }
 int fake_release_on(merf_scene_t s) { return merf::scene_release_on(s, reinterpret_cast<hipStream_t>(8)); }
 
 }  // extern "C"

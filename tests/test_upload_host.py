@@ -4,6 +4,7 @@ as much memory as a test gives it."""
 import ctypes as C
 import os
 import subprocess
+import time
 
 import numpy as np
 import pytest
@@ -77,3 +78,24 @@ def test_ordered_uploads_wait_for_no_other_work(lib, size):
     assert rc == 0 and lib.fake_waits() == before
     assert lib.fake_release_on(h) == 0 and lib.fake_waits() == before
     assert lib.merf_hbm_in_use() == 0 and lib.fake_held() == lib.fake_pool_kept()
+
+
+def test_ordered_release_keeps_what_would_have_to_wait(lib):
+    """Evicting the last scene frees its memory in stream order and no more;
+    the kept scratch and pinned buffers go back where the caller waits anyway."""
+    sc = SCENES["medium"]()
+    rc, h = upload(lib, sc, ordered=True)
+    assert rc == 0 and lib.fake_pinned() > 0 and lib.fake_pool_kept() > 0
+    time.sleep(1.1)                                # longer than memory is kept after its last use
+    before = lib.fake_waits()
+    assert lib.fake_release_on(h) == 0 and lib.fake_waits() == before
+    lib.fake_release_unused()
+    assert lib.fake_pinned() == lib.fake_held() == 0
+
+
+def test_free_gives_back_what_was_kept(lib):
+    rc, h = upload(lib, SCENES["medium"]())
+    assert rc == 0 and lib.fake_pinned() > 0 and lib.fake_pool_kept() > 0
+    time.sleep(1.1)
+    assert lib.merf_free(h) == 0
+    assert lib.fake_pinned() == lib.fake_held() == 0
