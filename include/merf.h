@@ -159,6 +159,7 @@ typedef struct {
  * Errors: MERF_E_INVALID for an inconsistent descriptor (sizes, block index
  * entries out of range, NULL arrays); MERF_E_OOM when the device bytes would
  * exceed the budget set by merf_set_hbm_budget or allocation fails.
+ * Memory kept for the next call: see merf_set_hbm_budget.
  */
 int merf_scene_upload(const merf_scene_desc *desc, merf_scene_t *out);
 
@@ -207,11 +208,25 @@ int merf_free(merf_scene_t s);
 /* Message of the calling thread's most recent error ("" if none). */
 const char *merf_last_error(void);
 
-/* Cap on device bytes held by all resident scenes (default: no cap).
- * Uploads that would exceed it fail with MERF_E_OOM. */
+/*
+ * Cap on device bytes held by all resident scenes (default: no cap).
+ * Uploads that would exceed it fail with MERF_E_OOM.
+ * Uploads and the empty-space grids keep memory for the next such call: device
+ * scratch, up to 256 MiB per device, and, once an upload from ordinary host
+ * memory has moved 4 MB, 16 MB of pinned host memory with four streams and
+ * eight events on one device.  Neither is in merf_hbm_in_use.  Scratch is kept
+ * only while the cap leaves 256 MiB beside the resident scenes, so scenes and
+ * a device's kept scratch together stay below it.  Every call of this function gives
+ * back what is kept and not in use; so do the release of the last scene and
+ * merf_server_destroy, for what was not used within the last second, and, for
+ * the scratch, a device allocation of this library that fails.  Otherwise it
+ * is held until the process ends.  (Giving pinned memory back waits for the
+ * device; a process that captures HIP graphs on other threads calls this
+ * function outside the capture, as it does hipHostFree.)
+ */
 int merf_set_hbm_budget(size_t bytes);
 
-/* Device bytes currently held by resident scenes. */
+/* Device bytes currently held by resident scenes (no scratch). */
 size_t merf_hbm_in_use(void);
 
 /* Device bytes held by scene s (0 for an invalid handle). */

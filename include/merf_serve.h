@@ -69,7 +69,9 @@ typedef struct {
     int32_t use_graphs;          /* 1: replay captured hipGraphs; 0: plain launches */
     int32_t evict_idle;          /* 1: evict idle scenes (least requested first) to admit a new one */
     int32_t pad;
-    size_t hbm_budget;           /* device bytes for resident scenes; 0 = no cap */
+    size_t hbm_budget;           /* device bytes for resident scenes; 0 = no cap
+                                    (scratch kept between uploads: see
+                                    merf_set_hbm_budget) */
 } merf_server_config;
 
 typedef struct {

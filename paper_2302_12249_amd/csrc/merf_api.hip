@@ -407,12 +407,6 @@ extern "C" {
 
 const char *merf_last_error(void) { return merf::g_error.c_str(); }
 
-int merf_set_hbm_budget(size_t bytes) {
-    std::lock_guard<std::mutex> lk(g_mutex);
-    g_budget = bytes;
-    return MERF_OK;
-}
-
 size_t merf_hbm_in_use(void) {
     std::lock_guard<std::mutex> lk(g_mutex);
     return g_in_use;
@@ -438,9 +432,12 @@ hipError_t dev_free(void *p, bool ordered, hipStream_t stream) {
 // library keeps for the next: device scratch (a memory pool per device that
 // holds on to at most kScratchKept bytes) and pinned host buffers (CopyRing).
 // Allocating and freeing them each time took 0.38 ms of an upload and half of
-// a 256^3 octant grid's 0.58 ms.  Both are given back when the last scene is
-// freed, unless they were used within the last second (scenes opened and
-// closed in turn), and the scratch also when a device allocation fails.
+// a 256^3 octant grid's 0.58 ms.  Both are given back by merf_set_hbm_budget,
+// when the last scene is freed or a server destroyed, unless they were used
+// within the last second (scenes opened and closed in turn), and the scratch
+// also when a device allocation of the library fails.  Scratch is kept only
+// while the budget has room for all that may be kept, so that scenes and kept
+// scratch together stay below it.
 constexpr size_t kScratchKept = (size_t)256 << 20, kScratchPooled = (size_t)1 << 20;
 constexpr int kScratchDevices = 16;
 constexpr auto kKeepAfterUse = std::chrono::seconds(1);
@@ -483,6 +480,23 @@ void trim_scratch() {
         if (pool) (void)hipMemPoolTrimTo(pool, 0);
 }
 
+// Whether the budget leaves n bytes beside the resident scenes.
+bool budget_room(size_t n) {
+    std::lock_guard<std::mutex> lk(g_mutex);
+    return g_budget >= g_in_use && g_budget - g_in_use >= n;
+}
+
+// A device allocation; kept scratch is given back if it fails at first.
+hipError_t dev_alloc_or_trim(void **p, size_t n, bool ordered, hipStream_t stream) {
+    hipError_t e = dev_alloc(p, n, ordered, stream);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        trim_scratch();
+        e = dev_alloc(p, n, ordered, stream);
+    }
+    return e;
+}
+
 // Scratch of n bytes, ordered on stream; from the pool up to its size, else
 // (and on a stream that is capturing) allocated and freed by dev_alloc and
 // dev_free, so that a stream-ordered upload's waits for nothing else on the
@@ -491,23 +505,20 @@ void trim_scratch() {
 // 1 MiB it turns).
 struct Scratch {
     void *p = nullptr;
-    bool by_stream = false;             // freed in stream order
+    bool by_stream = false, kept = false;       // freed in stream order; from the pool
     hipError_t alloc(size_t n, bool ordered, hipStream_t stream) {
-        hipMemPool_t pool = n >= kScratchPooled && n <= kScratchKept && !capturing(stream) ? scratch_pool() : nullptr;
-        by_stream = true;
+        const bool keep = n >= kScratchPooled && n <= kScratchKept && budget_room(kScratchKept);
+        hipMemPool_t pool = keep && !capturing(stream) ? scratch_pool() : nullptr;
+        by_stream = kept = true;
         if (pool && hipMallocFromPoolAsync(&p, n, pool, stream) == hipSuccess && p) return hipSuccess;
         if (pool) (void)hipGetLastError();
         by_stream = ordered;
-        hipError_t e = dev_alloc(&p, n, ordered, stream);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            trim_scratch();
-            e = dev_alloc(&p, n, ordered, stream);
-        }
-        return e;
+        kept = false;
+        return dev_alloc_or_trim(&p, n, ordered, stream);
     }
     void free(hipStream_t stream) {
         if (p) (void)dev_free(p, by_stream, stream);
+        if (p && kept && !budget_room(kScratchKept)) trim_scratch();    // scenes came meanwhile
         p = nullptr;
     }
 };
@@ -652,19 +663,18 @@ hipError_t upload_copies(const std::vector<Copy> &copies, bool ordered, hipStrea
     return staged.empty() ? hipSuccess : ring.run(staged);
 }
 
-// What was not used lately goes back (hipHostFree and hipStreamDestroy wait for
-// the device).
-void release_idle() {
-    const Clock::time_point now = Clock::now();
+// What is kept goes back, unless it is in use or was used later than `before`
+// (hipHostFree and hipStreamDestroy wait for the device).
+void release_kept(Clock::time_point before) {
     bool idle;
     {
         std::lock_guard<std::mutex> lk(g_scratch_mutex);
-        idle = now - g_scratch_used > kKeepAfterUse;
+        idle = g_scratch_used <= before;
     }
     if (idle) trim_scratch();
     CopyRing &ring = copy_ring();
     std::unique_lock<std::mutex> busy(ring.busy, std::try_to_lock);
-    if (busy.owns_lock() && now - ring.used > kKeepAfterUse) ring.release();
+    if (busy.owns_lock() && ring.used <= before) ring.release();
 }
 
 // merf_scene_upload (ordered = false: null stream, plain allocation) and
@@ -693,6 +703,7 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
             return fail(MERF_E_OOM, "scene needs %zu device bytes; %zu in use, budget %zu", total, g_in_use, g_budget);
         g_in_use += total;    // reserve; released below on failure
     }
+    if (!budget_room(kScratchKept)) trim_scratch();
     auto release = [&]() {
         std::lock_guard<std::mutex> lk(g_mutex);
         g_in_use -= total;
@@ -711,12 +722,7 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
                  staging = octants ? s_dist0 + octant_scratch_bytes((int)rf) : s_dist1 + align_up(nf, 256);
     void *base = nullptr;
     Scratch scratch;
-    hipError_t e = dev_alloc(&base, total, ordered, stream);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        trim_scratch();
-        e = dev_alloc(&base, total, ordered, stream);
-    }
+    hipError_t e = dev_alloc_or_trim(&base, total, ordered, stream);
     if (e == hipSuccess) e = scratch.alloc(staging, ordered, stream);
     // allocation failures surface here; and the copies use streams of their own
     if (e == hipSuccess && scratch.by_stream) e = hipStreamSynchronize(stream);
@@ -880,8 +886,9 @@ int scene_from_image_on(const SceneImage &img, const void *host, hipStream_t str
             return fail(MERF_E_OOM, "scene needs %zu device bytes; %zu in use, budget %zu", img.bytes, g_in_use, g_budget);
         g_in_use += img.bytes;
     }
+    if (!budget_room(kScratchKept)) trim_scratch();
     void *base = nullptr;
-    hipError_t e = hipMallocAsync(&base, img.bytes, stream);
+    hipError_t e = dev_alloc_or_trim(&base, img.bytes, true, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(base, host, img.bytes, hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess || !base) {
@@ -932,7 +939,7 @@ int scene_release_on(merf_scene_t s, hipStream_t stream) {
 }
 
 void release_unused() {
-    if (no_scene_left()) release_idle();
+    if (no_scene_left()) release_kept(Clock::now() - kKeepAfterUse);
 }
 
 }  // namespace merf
@@ -940,6 +947,15 @@ void release_unused() {
 extern "C" {
 
 int merf_scene_upload(const merf_scene_desc *desc, merf_scene_t *out) { return upload_impl(desc, out, false, nullptr); }
+
+int merf_set_hbm_budget(size_t bytes) {
+    {
+        std::lock_guard<std::mutex> lk(g_mutex);
+        g_budget = bytes;
+    }
+    release_kept(Clock::now());
+    return MERF_OK;
+}
 
 int merf_free(merf_scene_t s) {
     clear_error();

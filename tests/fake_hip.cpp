@@ -155,6 +155,16 @@ size_t fake_pinned() {
 size_t fake_peak(int reset) { const size_t v = peak; if (reset) peak = plain + pool_reserved(); return v; }
 long fake_waits() { return waits; }
 int fake_upload_on(const merf_scene_desc *d, merf_scene_t *out) { return merf::scene_upload_on(d, reinterpret_cast<hipStream_t>(8), out); }
+static merf::SceneImage image;
+static char *image_bytes = nullptr;
+int fake_image(merf_scene_t s) {
+    const size_t n = merf_scene_bytes(s);
+    image_bytes = static_cast<char *>(std::malloc(n));
+    return merf::scene_image_on(s, image_bytes, n, reinterpret_cast<hipStream_t>(8), &image);
+}
+int fake_restore(merf_scene_t *out) {
+    return merf::scene_from_image_on(image, image_bytes, reinterpret_cast<hipStream_t>(8), out);
+}
 void fake_release_unused() { merf::release_unused(); }
 int fake_release_on(merf_scene_t s) { return merf::scene_release_on(s, reinterpret_cast<hipStream_t>(8)); }
 

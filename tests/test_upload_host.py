@@ -39,12 +39,12 @@ def lib(so, tmp_path):
     with open(so, "rb") as f, open(path, "wb") as g:
         g.write(f.read())
     lib = C.CDLL(path)
-    for name in ("fake_held", "fake_pool_kept", "fake_pinned", "fake_peak", "merf_hbm_in_use"):
+    for name in ("fake_held", "fake_pool_kept", "fake_pinned", "fake_peak", "merf_hbm_in_use", "merf_scene_bytes"):
         getattr(lib, name).restype = C.c_size_t
     lib.fake_capacity.argtypes = [C.c_size_t]
     lib.merf_set_hbm_budget.argtypes = [C.c_size_t]
     lib.fake_waits.restype = C.c_long
-    lib.merf_free.argtypes = lib.fake_release_on.argtypes = [C.c_void_p]
+    lib.merf_free.argtypes = lib.merf_scene_bytes.argtypes = lib.fake_image.argtypes = lib.fake_release_on.argtypes = [C.c_void_p]
     lib.merf_last_error.restype = C.c_char_p
     return lib
 
@@ -99,3 +99,48 @@ def test_free_gives_back_what_was_kept(lib):
     time.sleep(1.1)
     assert lib.merf_free(h) == 0
     assert lib.fake_pinned() == lib.fake_held() == 0
+
+
+def test_setting_the_budget_gives_back_what_is_kept(lib):
+    rc, h = upload(lib, SCENES["medium"]())
+    assert rc == 0 and lib.merf_free(h) == 0       # within a second of its use
+    assert lib.fake_pinned() > 0 and lib.fake_pool_kept() > 0
+    assert lib.merf_set_hbm_budget(2 ** 63) == 0
+    assert lib.fake_pinned() == lib.fake_held() == 0
+
+
+def test_scenes_and_kept_scratch_stay_below_the_budget(lib):
+    sc = SCENES["medium"]()
+    rc, h = upload(lib, sc)
+    one = lib.merf_scene_bytes(h)
+    assert rc == 0 and lib.merf_free(h) == 0
+    room = 256 << 20                               # of scratch that may be kept
+    for spare in (0, room - 1, room):
+        budget = 3 * one + spare
+        assert lib.merf_set_hbm_budget(budget) == 0
+        hs = []
+        for i in range(3):
+            rc, h = upload(lib, sc, ordered=i == 1)
+            assert rc == 0 and lib.fake_held() <= budget
+            hs.append(h)
+        assert lib.merf_hbm_in_use() == 3 * one
+        assert (lib.fake_pool_kept() > 0) == (spare == room)
+        rc, h = upload(lib, sc)                    # scratch takes nothing from the scenes' share
+        assert rc == (merf.MERF_E_OOM if spare < one else 0) and lib.fake_held() <= budget
+        if rc == 0:
+            assert lib.merf_free(h) == 0
+        rc = [lib.fake_release_on(h) if i == 1 else lib.merf_free(h) for i, h in enumerate(hs)]
+        assert not any(rc)
+
+
+def test_kept_scratch_does_not_stand_in_the_way(lib):
+    """A device with room for a scene but not for the kept scratch beside it."""
+    sc = SCENES["medium"]()
+    rc, h = upload(lib, sc, ordered=True)
+    one = lib.merf_scene_bytes(h)
+    assert rc == 0 and lib.fake_image(h) == 0 and lib.fake_release_on(h) == 0
+    assert lib.fake_pool_kept() > 0
+    lib.fake_capacity(one)
+    back = C.c_void_p()
+    assert lib.fake_restore(C.byref(back)) == 0    # admitted again from its image
+    assert lib.fake_held() == one
