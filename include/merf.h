@@ -296,8 +296,10 @@ int merf_distance_grid(const uint8_t *const *occ_dev, const int32_t *res, int32_
  * finest cell, the largest E <= 255 such that the cube of E cells on a side
  * with a corner at the cell, extending in the octant's directions (clipped to
  * the grid), holds no cell that every level marks occupied; 0 for such a cell
- * itself.  Allocates 5 r^3 bytes of device scratch, runs on hip_stream and
- * returns once the grids are complete.
+ * itself.  With g = r^2 times r rounded up to 16, uses 10 g bytes of device
+ * scratch; for r > 256, or where the device or the cap of merf_set_hbm_budget
+ * has no room for them, 3 g bytes, more slowly (as merf_scene_upload does).
+ * Runs on hip_stream and returns once the grids are complete.
  * Errors: as merf_distance_grid.
  */
 int merf_octant_extent_grid(const uint8_t *const *occ_dev, const int32_t *res, int32_t n_levels, uint8_t *out_dev,

@@ -516,6 +516,19 @@ struct Scratch {
         kept = false;
         return dev_alloc_or_trim(&p, n, ordered, stream);
     }
+    // alloc, and usable when it returns from any stream: failures of a
+    // stream-ordered allocation surface here, and uploads copy on streams of
+    // their own.
+    hipError_t take(size_t n, bool ordered, hipStream_t stream) {
+        hipError_t e = alloc(n, ordered, stream);
+        if (e == hipSuccess && by_stream) e = hipStreamSynchronize(stream);
+        if (e == hipSuccess && !p) e = hipErrorOutOfMemory;
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            free(stream);
+        }
+        return e;
+    }
     void free(hipStream_t stream) {
         if (p) (void)dev_free(p, by_stream, stream);
         if (p && kept && !budget_room(kScratchKept)) trim_scratch();    // scenes came meanwhile
@@ -718,14 +731,20 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
     const size_t rf = (size_t)desc->occ_res[desc->occ_levels - 1], nf = rf * rf * rf;
     const bool octants = rf <= (size_t)kOctMaxRes;
     // scratch of the empty-space grid: the octants', or two byte grids
-    const size_t s_dist1 = s_dist0 + align_up(nf, 256),
-                 staging = octants ? s_dist0 + octant_scratch_bytes((int)rf) : s_dist1 + align_up(nf, 256);
+    const size_t s_dist1 = s_dist0 + align_up(nf, 256);
+    auto staging_of = [&](bool together) {
+        return octants ? s_dist0 + octant_scratch_bytes((int)rf, together) : s_dist1 + align_up(nf, 256);
+    };
+    bool together = octants && budget_room(staging_of(true));
     void *base = nullptr;
     Scratch scratch;
     hipError_t e = dev_alloc_or_trim(&base, total, ordered, stream);
-    if (e == hipSuccess) e = scratch.alloc(staging, ordered, stream);
-    // allocation failures surface here; and the copies use streams of their own
-    if (e == hipSuccess && scratch.by_stream) e = hipStreamSynchronize(stream);
+    if (e == hipSuccess) e = scratch.take(staging_of(together), ordered, stream);
+    if (e != hipSuccess && base && together) {
+        together = false;
+        e = scratch.take(staging_of(false), ordered, stream);
+    }
+    const size_t staging = staging_of(together);
     void *stage = scratch.p;
     if (e != hipSuccess || !base || !stage) {
         (void)hipGetLastError();
@@ -764,7 +783,7 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
             lv.occ[l] = dev(o_occ[l]);
             lv.res[l] = desc->occ_res[l];
         }
-        e = octants ? launch_octant_extents(lv, stg(s_dist0), dev(lay.dist), stream)
+        e = octants ? launch_octant_extents(lv, together, stg(s_dist0), dev(lay.dist), stream)
                     : launch_distance_grid(lv, stg(s_dist0), stg(s_dist1), dev(lay.dist), stream);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
@@ -1195,15 +1214,22 @@ int merf_octant_extent_grid(const uint8_t *const *occ_dev, const int32_t *res, i
     OccLevels lv;
     int rc = occ_levels_arg(occ_dev, res, n_levels, out_dev, lv);
     if (rc) return rc;
-    const size_t bytes = octant_scratch_bytes(res[n_levels - 1]);
+    const int r = res[n_levels - 1];
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    // the octants together where there is room for their scratch, else one
+    // after another
+    bool together = r <= kOctMaxRes && budget_room(octant_scratch_bytes(r, true));
     Scratch tmp;
-    hipError_t e = tmp.alloc(bytes, false, stream);
-    if (e != hipSuccess || !tmp.p) {
+    if (together) together = tmp.alloc(octant_scratch_bytes(r, true), false, stream) == hipSuccess && tmp.p;
+    if (!together) {
+        const size_t bytes = octant_scratch_bytes(r, false);
         (void)hipGetLastError();
-        return fail(MERF_E_OOM, "hipMalloc of %zu scratch bytes failed", bytes);
+        if (tmp.alloc(bytes, false, stream) != hipSuccess || !tmp.p) {
+            (void)hipGetLastError();
+            return fail(MERF_E_OOM, "hipMalloc of %zu scratch bytes failed", bytes);
+        }
     }
-    e = launch_octant_extents(lv, static_cast<uint8_t *>(tmp.p), out_dev, stream);
+    hipError_t e = launch_octant_extents(lv, together, static_cast<uint8_t *>(tmp.p), out_dev, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     tmp.free(stream);
     if (e != hipSuccess) return hip_fail(e, "octant extent grid");

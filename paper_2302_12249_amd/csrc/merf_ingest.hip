@@ -504,22 +504,14 @@ __global__ __launch_bounds__(64) void k_extents(const OctantScratch sc, int firs
 
 }  // namespace
 
-// The eight octants together need 10 padded grids of scratch; above
-// kOctMaxRes (which no upload needs) they are built one after another from
-// three.
-size_t octant_scratch_bytes(int r) {
-    const size_t grid = (size_t)r * r * ((size_t)(r + 15) / 16 * 16);
-    return grid * (r <= kOctMaxRes ? 10 : 3);
-}
-
 namespace {
 
 template <int N>
-hipError_t octant_extents(const OccLevels &lv, uint8_t *scratch, uint8_t *out, hipStream_t stream) {
+hipError_t octant_extents(const OccLevels &lv, bool together, uint8_t *scratch, uint8_t *out, hipStream_t stream) {
     OctantScratch sc{};
     sc.r = lv.res[lv.n - 1];
     sc.rp = (sc.r + 15) / 16 * 16;
-    sc.single = sc.r > kOctMaxRes;
+    sc.single = !together;
     const size_t r = (size_t)sc.r, n = r * r * r, grid = r * r * (size_t)sc.rp;
     const unsigned rows = 64u / (unsigned)(sc.rp / N);        // rows of a wave
     const size_t run_rows = 64u / (unsigned)(sc.rp / 16) * kRunWaves;         // rows of a workgroup of k_runs_x
@@ -554,10 +546,11 @@ hipError_t octant_extents(const OccLevels &lv, uint8_t *scratch, uint8_t *out, h
 
 // The marching steps: a row of up to 256 cells takes at most 64 lanes of four
 // (few lines march, so each takes more lanes); larger ones have 16 cells a lane.
-hipError_t launch_octant_extents(const OccLevels &lv, uint8_t *scratch, uint8_t *out, hipStream_t stream) {
+hipError_t launch_octant_extents(const OccLevels &lv, bool together, uint8_t *scratch, uint8_t *out, hipStream_t stream) {
     const int r = lv.res[lv.n - 1];
-    if (r <= 0 || r > kMaxDistRes) return hipErrorInvalidValue;
-    return r <= 256 ? octant_extents<4>(lv, scratch, out, stream) : octant_extents<16>(lv, scratch, out, stream);
+    if (r <= 0 || r > kMaxDistRes || (together && r > kOctMaxRes)) return hipErrorInvalidValue;
+    return r <= 256 ? octant_extents<4>(lv, together, scratch, out, stream)
+                    : octant_extents<16>(lv, together, scratch, out, stream);
 }
 
 hipError_t launch_pack_bricks(const uint8_t *blocks, const int32_t *block_index, const int32_t *brick_pos,

@@ -28,6 +28,7 @@ size_t capacity = SIZE_MAX, plain = 0;
 Pool *only = nullptr;                 // one scratch pool (one device)
 size_t pool_reserved() { return only ? only->reserved : 0; }
 size_t peak = 0;
+bool octants_together = false;
 long waits = 0;                       // hipFree, hipHostFree, hipStreamDestroy, hipDeviceSynchronize
 hipError_t last = hipSuccess;
 
@@ -153,6 +154,7 @@ size_t fake_pinned() {
     return n;
 }
 size_t fake_peak(int reset) { const size_t v = peak; if (reset) peak = plain + pool_reserved(); return v; }
+int fake_octants_together() { return octants_together; }
 long fake_waits() { return waits; }
 int fake_upload_on(const merf_scene_desc *d, merf_scene_t *out) { return merf::scene_upload_on(d, reinterpret_cast<hipStream_t>(8), out); }
 static merf::SceneImage image;
@@ -180,9 +182,9 @@ hipError_t launch_pack_bricks(const uint8_t *, const int32_t *, const int32_t *,
 hipError_t launch_distance_grid(const OccLevels &, uint8_t *, uint8_t *, uint8_t *, hipStream_t) { return hipSuccess; }
 hipError_t launch_mlp_fragments(const float *, uint32_t *, hipStream_t) { return hipSuccess; }
 hipError_t launch_identity_order(int32_t *, int, hipStream_t) { return hipSuccess; }
-size_t octant_scratch_bytes(int r) { return (size_t)r * r * ((size_t)(r + 15) / 16 * 16) * (r <= kOctMaxRes ? 10 : 3); }
-hipError_t launch_octant_extents(const OccLevels &lv, uint8_t *scratch, uint8_t *, hipStream_t) {
-    return room(scratch) >= octant_scratch_bytes(lv.res[lv.n - 1]) ? hipSuccess : hipErrorInvalidValue;
+hipError_t launch_octant_extents(const OccLevels &lv, bool together, uint8_t *scratch, uint8_t *, hipStream_t) {
+    octants_together = together;
+    return room(scratch) >= octant_scratch_bytes(lv.res[lv.n - 1], together) ? hipSuccess : hipErrorInvalidValue;
 }
 
 }  // namespace merf

@@ -144,3 +144,49 @@ def test_kept_scratch_does_not_stand_in_the_way(lib):
     back = C.c_void_p()
     assert lib.fake_restore(C.byref(back)) == 0    # admitted again from its image
     assert lib.fake_held() == one
+
+
+def octants(lib, r):
+    occ, out = np.zeros(r ** 3, np.uint8), np.zeros(8, np.uint8)
+    levels, res = (C.c_void_p * 1)(occ.ctypes.data), (C.c_int32 * 1)(r)
+    return lib.merf_octant_extent_grid(levels, res, 1, C.c_void_p(out.ctypes.data), None)
+
+
+@pytest.mark.parametrize("r", [16, 96, 100, 256, 272])
+def test_octant_grids_need_no_more_memory_than_five_grids(lib, r):
+    """A device with 5 r^3 bytes free (a little more where rows are padded by
+    much) builds the grids, one octant after another."""
+    assert octants(lib, r) == 0 and lib.fake_octants_together() == (r <= 256)
+    lib.merf_set_hbm_budget(2 ** 64 - 1)
+    lib.fake_capacity(5 * r ** 3)
+    assert octants(lib, r) == 0 and not lib.fake_octants_together()
+    assert lib.fake_held() <= 5 * r ** 3
+    lib.fake_capacity(2 * r ** 3)
+    assert octants(lib, r) == merf.MERF_E_OOM and lib.fake_held() == 0
+
+
+def test_octants_respect_the_budget(lib):
+    lib.merf_set_hbm_budget(10 * 64 ** 3 - 1)
+    assert octants(lib, 64) == 0 and not lib.fake_octants_together()
+    lib.merf_set_hbm_budget(10 * 64 ** 3)
+    assert octants(lib, 64) == 0 and lib.fake_octants_together()
+
+
+@pytest.mark.parametrize("ordered", [False, True])
+def test_uploads_fit_where_they_did(lib, ordered):
+    """Memory for the scene, its staging and five grids beside them."""
+    sc = dense_scene(L=64, R=64)
+    r = 128
+    sc.occ = [(r, np.ones((r, r, r), np.uint8))]
+    rc, h = upload(lib, sc, ordered)
+    one = lib.merf_scene_bytes(h)
+    assert rc == 0 and lib.fake_octants_together()
+    assert (lib.fake_release_on(h) if ordered else lib.merf_free(h)) == 0
+    lib.merf_set_hbm_budget(2 ** 64 - 1)
+    staging = sc.blocks.nbytes + sc.block_index.nbytes + 4 * 8 ** 3
+    lib.fake_capacity(one + staging + 5 * r ** 3)
+    rc, h = upload(lib, sc, ordered)
+    assert rc == 0 and not lib.fake_octants_together()
+    lib.fake_capacity(one + staging + r ** 3)
+    assert upload(lib, sc, ordered)[0] == merf.MERF_E_OOM
+    assert lib.merf_hbm_in_use() == one == lib.fake_held()
