@@ -10,9 +10,10 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <unordered_set>
 #include <vector>
@@ -208,8 +209,12 @@ namespace merf {
 const DevScene *scene_dev(merf_scene_t s) { return live(s) ? &s->ds : nullptr; }
 
 size_t scene_device_bytes(const merf_scene_desc *desc) {
-    if (validate_desc(desc) != MERF_OK) return 0;
-    return make_layout(desc, count_bricks(desc)).total;
+    try {
+        if (validate_desc(desc) != MERF_OK) return 0;
+        return make_layout(desc, count_bricks(desc)).total;
+    } catch (const std::bad_alloc &) {
+        return 0;
+    }
 }
 
 namespace {
@@ -623,7 +628,7 @@ struct CopyRing {
         const int want = (int)std::min<size_t>(kCopyThreads, pieces.size());
         try {
             for (int t = 1; t < want; ++t) threads.emplace_back(work, t);
-        } catch (const std::system_error &) {       // no more threads: those there are do it
+        } catch (const std::exception &) {          // no more threads (or no memory for one): those there are do it
         }
         work(0);
         for (std::thread &t : threads) t.join();
@@ -691,7 +696,8 @@ void release_kept(Clock::time_point before) {
 }
 
 // merf_scene_upload (ordered = false: null stream, plain allocation) and
-// scene_upload_on (ordered = true: everything on stream).
+// scene_upload_on (ordered = true: everything on stream).  Host memory that may
+// fail is taken before device memory, or given back with it.
 int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hipStream_t stream) {
     clear_error();
     if (!out) return fail(MERF_E_INVALID, "output handle pointer is NULL");
@@ -709,6 +715,9 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
     const Layout lay = make_layout(desc, nbricks);
     const size_t o_bidx = lay.bidx, o_bricks = lay.bricks, o_planes = lay.planes, o_mlp = lay.mlp, total = lay.total;
     const size_t *o_occ = lay.occ;
+    std::vector<Copy> copies;
+    copies.reserve(6 + kMaxLevels);
+    std::unique_ptr<merf_scene> scene(new merf_scene());
 
     {
         std::lock_guard<std::mutex> lk(g_mutex);
@@ -756,7 +765,7 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
     }
     auto dev = [&](size_t o) { return static_cast<uint8_t *>(base) + o; };
     auto stg = [&](size_t o) { return static_cast<uint8_t *>(stage) + o; };
-    std::vector<Copy> copies = {
+    copies = {
         {dev(o_bidx), bidx.data(), bidx.size() * sizeof(int32_t)},
         {dev(o_planes), desc->planes, (size_t)3 * R * R * kChannels},
         {dev(o_mlp), desc->mlp_params, kMlpParams * sizeof(float)},
@@ -768,7 +777,11 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
         size_t r = (size_t)desc->occ_res[l];
         copies.push_back({dev(o_occ[l]), desc->occ[l], r * r * r});
     }
-    e = upload_copies(copies, ordered, stream);
+    try {
+        e = upload_copies(copies, ordered, stream);
+    } catch (const std::bad_alloc &) {
+        e = hipErrorOutOfMemory;
+    }
     if (e == hipSuccess && R == 0) e = hipMemsetAsync(dev(o_planes), 0, (size_t)3 * 2 * 2 * kChannels, stream);
     if (e == hipSuccess)
         e = launch_pack_bricks(stg(s_blocks), reinterpret_cast<const int32_t *>(stg(s_index)),
@@ -788,14 +801,17 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
     }
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     scratch.free(stream);
-    if (e != hipSuccess) {
+    auto undo = [&]() {
         (void)dev_free(base, ordered, stream);
         if (ordered) (void)hipStreamSynchronize(stream);
         release();
+    };
+    if (e != hipSuccess) {
+        undo();
         return hip_fail(e, "scene upload");
     }
 
-    merf_scene *s = new merf_scene();
+    merf_scene *s = scene.get();
     s->magic = kMagic;
     s->dev_base = base;
     s->dev_bytes = total;
@@ -848,12 +864,23 @@ int upload_impl(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hi
     constexpr double kNegLog2e = -1.4426950408889634;
     ds.f_scale24_l2 = (float)(kNegLog2e * (double)ds.f_scale24);
     ds.f_off_l2 = (float)(kNegLog2e * (double)ds.f_off);
-    {
+    try {
         std::lock_guard<std::mutex> lk(g_mutex);
         g_live.insert(s);
+    } catch (const std::bad_alloc &) {
+        undo();
+        throw;
     }
-    *out = s;
+    *out = scene.release();
     return MERF_OK;
+}
+
+int upload(const merf_scene_desc *desc, merf_scene_t *out, bool ordered, hipStream_t stream) {
+    try {
+        return upload_impl(desc, out, ordered, stream);
+    } catch (const std::bad_alloc &) {
+        return fail(MERF_E_OOM, "no host memory for the upload");
+    }
 }
 
 // Forget a live scene and return its memory to the budget; false if s is
@@ -876,7 +903,7 @@ bool no_scene_left() {
 namespace merf {
 
 int scene_upload_on(const merf_scene_desc *desc, hipStream_t stream, merf_scene_t *out) {
-    return upload_impl(desc, out, true, stream);
+    return upload(desc, out, true, stream);
 }
 
 int scene_image_on(merf_scene_t s, void *host, size_t host_bytes, hipStream_t stream, SceneImage *img) {
@@ -965,7 +992,7 @@ void release_unused() {
 
 extern "C" {
 
-int merf_scene_upload(const merf_scene_desc *desc, merf_scene_t *out) { return upload_impl(desc, out, false, nullptr); }
+int merf_scene_upload(const merf_scene_desc *desc, merf_scene_t *out) { return upload(desc, out, false, nullptr); }
 
 int merf_set_hbm_budget(size_t bytes) {
     {

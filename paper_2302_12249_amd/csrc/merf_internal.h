@@ -57,7 +57,8 @@ int scene_from_image_on(const SceneImage &img, const void *host, hipStream_t str
 // Device view of a live scene handle, or nullptr.
 const DevScene *scene_dev(merf_scene_t s);
 
-// Device bytes merf_scene_upload would allocate for desc (0 if desc is invalid).
+// Device bytes merf_scene_upload would allocate for desc (0 if desc is invalid
+// or there is no host memory to tell).
 size_t scene_device_bytes(const merf_scene_desc *desc);
 
 // Validate render parameters; res is the finest scene resolution max(R, L),

@@ -9,6 +9,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 
 #include "merf_internal.h"
 
@@ -23,6 +24,13 @@ struct Block {
     Pool *pool;                       // of a pool allocation
 };
 std::mutex mu;
+// the fail_at-th allocation of the code under test throws (0: none)
+long fail_at = 0;
+thread_local int inside = 0;          // this file's own allocations never do
+struct Own {
+    Own() { ++inside; }
+    ~Own() { --inside; }
+};
 std::map<void *, Block> device, host;
 size_t capacity = SIZE_MAX, plain = 0;
 Pool *only = nullptr;                 // one scratch pool (one device)
@@ -37,6 +45,7 @@ hipError_t done(hipError_t e) {
     return e;
 }
 hipError_t take(void **p, size_t n, Pool *pool) {
+    Own own;
     std::lock_guard<std::mutex> lk(mu);
     *p = nullptr;
     const size_t grow = pool ? std::max(pool->reserved, pool->used + n) - pool->reserved : n;
@@ -79,6 +88,14 @@ size_t room(const void *p) {
 
 }  // namespace
 
+void *operator new(size_t n) {
+    if (!inside && fail_at > 0 && __atomic_sub_fetch(&fail_at, 1, __ATOMIC_RELAXED) == 0) throw std::bad_alloc();
+    if (void *p = std::malloc(std::max<size_t>(n, 1))) return p;
+    throw std::bad_alloc();
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+
 extern "C" {
 
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
@@ -92,6 +109,7 @@ hipError_t hipFree(void *p) { ++waits; return give(p); }
 hipError_t hipMallocAsync(void **p, size_t n, hipStream_t) { return take(p, n, nullptr); }
 hipError_t hipFreeAsync(void *p, hipStream_t) { return give(p); }
 hipError_t hipMemPoolCreate(hipMemPool_t *p, const hipMemPoolProps *) {
+    Own own;
     only = new Pool();
     *p = reinterpret_cast<hipMemPool_t>(only);
     return hipSuccess;
@@ -111,6 +129,7 @@ hipError_t hipMallocFromPoolAsync(void **p, size_t n, hipMemPool_t pool, hipStre
     return take(p, n, reinterpret_cast<Pool *>(pool));
 }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
+    Own own;
     *p = std::malloc(n);
     std::lock_guard<std::mutex> lk(mu);
     host[*p] = {n, nullptr};
@@ -155,6 +174,8 @@ size_t fake_pinned() {
 }
 size_t fake_peak(int reset) { const size_t v = peak; if (reset) peak = plain + pool_reserved(); return v; }
 int fake_octants_together() { return octants_together; }
+// the n-th allocation from now on fails; returns how many are left of that
+long fake_fail_new(long n) { const long left = fail_at; fail_at = n; return left; }
 long fake_waits() { return waits; }
 int fake_upload_on(const merf_scene_desc *d, merf_scene_t *out) { return merf::scene_upload_on(d, reinterpret_cast<hipStream_t>(8), out); }
 static merf::SceneImage image;

@@ -4,6 +4,7 @@ as much memory as a test gives it."""
 import ctypes as C
 import os
 import subprocess
+import sys
 import time
 
 import numpy as np
@@ -38,12 +39,16 @@ def lib(so, tmp_path):
     path = str(tmp_path / "libmerf_fake.so")
     with open(so, "rb") as f, open(path, "wb") as g:
         g.write(f.read())
-    lib = C.CDLL(path)
+    return declare(C.CDLL(path))
+
+
+def declare(lib):
     for name in ("fake_held", "fake_pool_kept", "fake_pinned", "fake_peak", "merf_hbm_in_use", "merf_scene_bytes"):
         getattr(lib, name).restype = C.c_size_t
     lib.fake_capacity.argtypes = [C.c_size_t]
     lib.merf_set_hbm_budget.argtypes = [C.c_size_t]
-    lib.fake_waits.restype = C.c_long
+    lib.fake_waits.restype = lib.fake_fail_new.restype = C.c_long
+    lib.fake_fail_new.argtypes = [C.c_long]
     lib.merf_free.argtypes = lib.merf_scene_bytes.argtypes = lib.fake_image.argtypes = lib.fake_release_on.argtypes = [C.c_void_p]
     lib.merf_last_error.restype = C.c_char_p
     return lib
@@ -190,3 +195,43 @@ def test_uploads_fit_where_they_did(lib, ordered):
     lib.fake_capacity(one + staging + r ** 3)
     assert upload(lib, sc, ordered)[0] == merf.MERF_E_OOM
     assert lib.merf_hbm_in_use() == one == lib.fake_held()
+
+
+SWEEP = """
+import sys
+sys.path[:0] = [{root!r}, {here!r}]
+import ctypes as C
+import test_upload_host as T
+from scene_builders import dense_scene
+from paper_2302_12249_amd import merf
+lib = T.declare(C.CDLL({so!r}))
+sc = dense_scene(L=16, R=512)
+for ordered in (False, True):
+    n, failed = 0, 0
+    while True:
+        n += 1
+        lib.fake_fail_new(n)
+        rc, h = T.upload(lib, sc, ordered)
+        left = lib.fake_fail_new(0)
+        assert rc in (0, merf.MERF_E_OOM, merf.MERF_E_DEVICE), rc
+        failed += rc != 0
+        if rc == 0:
+            assert (lib.fake_release_on(h) if ordered else lib.merf_free(h)) == 0
+        assert lib.merf_hbm_in_use() == 0 and lib.fake_held() == lib.fake_pool_kept(), (n, rc)
+        if left > 0:
+            break
+    print(ordered, n, failed, flush=True)
+    assert failed > 5
+"""
+
+
+def test_uploads_without_host_memory_fail_cleanly(so, tmp_path):
+    """Each allocation of an upload fails in turn (those of the copying threads
+    among them): an error code or an upload all the same, and nothing left.  In
+    a process of its own, which an exception in the wrong place would end."""
+    path = str(tmp_path / "libmerf_fake.so")
+    with open(so, "rb") as f, open(path, "wb") as g:
+        g.write(f.read())
+    code = SWEEP.format(root=os.path.dirname(HERE), here=HERE, so=path)
+    p = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
+    assert p.returncode == 0, p.stdout + p.stderr
