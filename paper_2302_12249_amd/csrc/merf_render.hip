@@ -391,14 +391,19 @@ __device__ __forceinline__ SampleResult eval_sample(const S &sc, float3 p, float
     // (appearance of every lane: where alpha is zero its weight is zero, and
     // a wave with no other lane practically never occurs)
     {
-        // The 210 eight-byte instructions that follow run faster from 4 modulo
-        // 8 bytes than from 0: a four-byte instruction moved across this point
-        // made kernels 2.5% faster or slower whatever else it did, so the
-        // place is fixed here (against 0: sixteen 1080p views 3.06 -> 2.97 ms,
-        // 4K with the bf16 MLP 1.176 -> 1.135 ms; aligning the march or the
-        // density as well changes nothing).
+        // The eight-byte vector instructions that follow (210 of them, 330
+        // with float16 features) run faster from 4 modulo 8 bytes than from 0:
+        // a four-byte instruction moved across this point made kernels 2.5%
+        // faster or slower whatever else it did, so the place is fixed here
+        // (float32 features, against 0: sixteen 1080p views 3.06 -> 2.97 ms, a
+        // 4K frame with the bf16 MLP 1.176 -> 1.135 ms, a 1080p view 219.7 ->
+        // 213.2 us).  With float16 features (kFeat 1) an odd number of
+        // four-byte instructions comes first, so they start from 0 (333 -> 322
+        // us).  The few of kFeat 2 do not care: 221.7 us wherever they are.
+        // Aligning the march or the density as well changes nothing.
         __builtin_amdgcn_sched_barrier(0);
-        asm volatile(".p2align 3\n s_nop 0");
+        if constexpr (kFeat == 0) asm volatile(".p2align 3\n s_nop 0");
+        else if constexpr (kFeat == 1) asm volatile(".p2align 3");
         __builtin_amdgcn_sched_barrier(0);
         float sa[7];
 #pragma unroll
