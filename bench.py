@@ -57,7 +57,8 @@ VALU_F32_PEAK_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
 # everything that decides what the render kernel reads and how (kernel, scene
 # layout, brick packing); counters taken on other sources are stale
 KERNEL_SOURCES = ["paper_2302_12249_amd/csrc/merf_render.hip", "paper_2302_12249_amd/csrc/merf_device.h",
-                  "paper_2302_12249_amd/csrc/merf_api.hip", "paper_2302_12249_amd/csrc/merf_ingest.hip"]
+                  "paper_2302_12249_amd/csrc/merf_segments.h", "paper_2302_12249_amd/csrc/merf_api.hip",
+                  "paper_2302_12249_amd/csrc/merf_ingest.hip"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "render_full_1080p_traffic.json")
 MFMA_FILE = os.path.join(ROOT, "profiles", "render_full_1080p_mfma.json")
 # the deferred MLP per pixel: 34 x 16 + 16 x 16 + 16 x 3 multiply-adds (App. B)

@@ -144,7 +144,11 @@ typedef struct {
                                              (skip_mode 0: distance-grid lookups),
                                              [2] lattice samples visited, [3] samples
                                              evaluated, [4] samples with alpha > 0,
-                                             [5] rays terminated early, [6..7] 0 */
+                                             [5] rays terminated early, [6..7] 0.
+                                             [1] and [2] count the march's work, some
+                                             of it ahead of where a ray then ends, so
+                                             they follow the kernel (a few parts per
+                                             thousand); the others do not */
 } merf_render_params;
 
 /*

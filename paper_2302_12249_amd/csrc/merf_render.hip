@@ -20,8 +20,8 @@
 //      one brick per sample thanks to the apron) and the three planes
 //      (bilinear), dequantise (Eq. 8; the fp32 path applies it to the
 //      interpolated codes, the same value up to rounding), sum (Eq. 5),
-//      decode (Eq. 6) -- density first, appearance only when alpha != 0;
-//      each lane then composites its own samples in ray order (Eq. 1-2);
+//      decode (Eq. 6); each lane then composites its own samples in ray
+//      order (Eq. 1-2);
 //   5. marching stops when the transmittance drops below t_min (Sec. 6);
 //   6. the deferred MLP h(C_d, F, d) runs once per pixel (Eq. 3, App. B).
 // Before a launch, a prepass (k_tile_cost, k_tile_order) marches a few
@@ -276,8 +276,8 @@ struct Texels {
 // Issue every load of a sample before waiting on any: the brick index first
 // (the brick loads depend on it), then the plane pairs, which overlap its
 // round trip, then the brick pairs.  The empty asm takes all ten vectors, so
-// the compiler neither splits them into per-word loads nor sinks any behind
-// the alpha test, and places one wait before it.  Every array is present on
+// the compiler neither splits them into per-word loads nor sinks any to their
+// first use, and places one wait before it.  Every array is present on
 // the device (a scene without a grid or without planes reads an all-zero
 // stand-in), so nothing here branches.
 template <typename S>
@@ -301,8 +301,8 @@ __device__ __forceinline__ Texels gather(const S &sc, const Footprint &f) {
     return x;
 }
 
-// Shaded sample: 1 - alpha and, when alpha != 0, the sigmoids of the diffuse
-// colour and the features (Eq. 6).
+// Shaded sample: 1 - alpha and the sigmoids of the diffuse colour and the
+// features (Eq. 6).
 struct SampleResult {
     float trans;
     float sg[7];
@@ -361,7 +361,7 @@ __device__ __forceinline__ SampleResult eval_sample(const S &sc, float3 p, float
     // summed by one dot product with FP32 accumulation (v_dot2_f32_f16).
     // (a = d_scale or f_scale, n m = -d_off or -f_off, precomputed)
     const float md = sc.m_density, mf = sc.m_feature;
-    // ---- density first (Sec. 6): appearance is read only when alpha != 0
+    // ---- density
     float s0 = 0.0f;
     if constexpr (kFeat == 1) {
         // a stand-in source (scene without grid or without planes) reads code
@@ -388,8 +388,9 @@ __device__ __forceinline__ SampleResult eval_sample(const S &sc, float3 p, float
     SampleResult r;
     float tau = __expf(s0);                       // Eq. 6
     r.trans = __expf(-tau * delta);               // e^{-tau delta} = 1 - alpha (Eq. 1)
-    // (appearance of every lane: where alpha is zero its weight is zero, and
-    // a wave with no other lane practically never occurs)
+    // ---- appearance, of every lane: where alpha is zero its weight is zero,
+    // and a wave with no other lane practically never occurs (Sec. 6 reads it
+    // only where alpha is not zero)
     {
         // The eight-byte vector instructions that follow (210 of them, 330
         // with float16 features) run faster from 4 modulo 8 bytes than from 0:
