@@ -14,6 +14,7 @@ import dataclasses
 import numpy as np
 import pytest
 
+import oracle
 import synth
 from scene_builders import dense_scene
 
@@ -95,3 +96,40 @@ def test_mlp_of_colours_and_features(torch, merf, lit, scale, rows):
         print(f"inputs {size} weights {scale} {rows}, {name}: max err {np.max(err[x.all(1)] / top[x.all(1)]):.2e} of the sums of magnitudes, "
               f"norm {np.linalg.norm(err) / np.linalg.norm(y):.2e}", flush=True)
         assert np.all(err <= bound)
+
+
+def _direction():
+    w, h = (int(v) for v in CAMS.size[0])
+    r, c = np.divmod(np.arange(w * h), w)
+    _, d = oracle.camera_rays(CAMS, 0, r, c)
+    return np.concatenate([d] + [np.sin(2.0 ** k * d) for k in range(4)] + [np.cos(2.0 ** k * d) for k in range(4)], 1)
+
+
+@pytest.mark.parametrize("scale", [0.1, 1.0, 100.0])
+@pytest.mark.parametrize("direction", [True, False])
+def test_mlp_error_next_to_float32_instructions(torch, merf, lit, scale, direction):
+    """2-norm of the error, six MLPs of normal weights.  With weights on every
+    input it is no larger than the float32 instructions' (whose mode takes the
+    hardware's sines).  With none on the direction only the split differs: two
+    operands off by a 2^-24 (rms) each at every product, where a float32 product
+    rounds once, stay within four times their error; colours of 1e-5 alone are
+    too far below the bound of the hidden units for that."""
+    size, sc, x = lit
+    X = np.concatenate([x, _direction()], 1)
+    norms = {"float32 instructions": [], "default": []}
+    for seed in range(6):
+        rng = np.random.default_rng(seed)
+        W0, W1, W2 = (scale * rng.normal(size=s) for s in ((34, 16), (16, 16), (16, 3)))
+        if not direction:
+            W0[7:] = 0.0
+        w = [np.float32(a).astype(np.float64) for a in (W0, W1, W2)]
+        y = np.maximum(np.maximum(X @ w[0], 0.0) @ w[1], 0.0) @ w[2] + x[:, :3]
+        exact = _pack(W0.astype(np.float32) * np.float32(2.0 ** 60), W1.astype(np.float32) * np.float32(2.0 ** -60), W2)
+        for name, mlp in (("float32 instructions", exact), ("default", _pack(W0, W1, W2))):
+            norms[name].append(np.linalg.norm(_rgb(torch, merf, sc, mlp) - y) / np.linalg.norm(y))
+    a, b = (float(np.sqrt(np.mean(np.square(v)))) for v in norms.values())
+    print(f"inputs {size} weights {scale} direction {direction}: float32 instructions {a:.2e}, default {b:.2e}", flush=True)
+    if direction:
+        assert b <= a
+    elif size != "1e-5":
+        assert b <= 4 * a
